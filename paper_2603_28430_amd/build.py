@@ -46,7 +46,8 @@ def build(verbose: bool = False) -> str:
     inc = [f"-I{INCLUDE}", f"-I{CSRC}"]
     jobs = []
     for src in ("isoq_kernels.hip", "isoq_kernels_8d.hip", "isoq_kernels_m.hip", "isoq_scores.hip",
-                "isoq_scores_8d.hip", "isoq_scores_qjl.hip", "isoq_qjl.hip", "isoq_generic_full.hip", "isoq_generic_fast.hip",
+                "isoq_scores_8d.hip", "isoq_scores_qjl.hip", "isoq_scores_m.hip", "isoq_scores_m64.hip",
+                "isoq_scores_m128.hip", "isoq_qjl.hip", "isoq_generic_full.hip", "isoq_generic_fast.hip",
                 "isoq_generic_2d.hip", "isoq_generic_8d.hip", "isoq_qjl_append.hip", "isoq_packed.hip",
                 "isoq_packed_8d.hip", "isoq_packed_qjl.hip", "isoq_scores_generic.hip"):
         jobs.append([HIPCC, *DEVICE_FLAGS, *inc, "-c", os.path.join(CSRC, src), "-o",

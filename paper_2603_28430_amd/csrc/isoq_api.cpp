@@ -23,6 +23,9 @@ struct isoq_params {
     float lut_inv_h;
     std::vector<float> exported;    // unit parameters as used (Table 1 layout)
     float levels[16], thresholds[15];
+    isoq::LevelDigits lv;             // levels as digits (the first set)
+    size_t lv_offset;               // floats from dparams to the further sets
+    int n_pass;                     // sets in all
 };
 
 struct isoq_sketch {
@@ -406,6 +409,23 @@ isoq_status isoq_params_init(isoq_params **out, int variant, int d, int bits, in
         layout.insert(layout.end(), f, f + mf.size() / 2);
     }
 
+    // the levels as digits for the logits; sets after the first go to the
+    // device with the rest
+    std::vector<LevelDigits> lv;
+    try {
+        build_level_digits(bits, p->levels, lv);
+        while (layout.size() % 4)
+            layout.push_back(0.f);
+        p->lv = lv[0];
+        p->n_pass = (int)lv.size();
+        p->lv_offset = layout.size();
+        const float *f = reinterpret_cast<const float *>(lv.data() + 1);
+        layout.insert(layout.end(), f, f + (lv.size() - 1) * (sizeof(LevelDigits) / sizeof(float)));
+    } catch (const std::bad_alloc &) {
+        delete p;
+        return ISOQ_E_NOMEM;
+    }
+
     hipError_t e = hipGetDevice(&p->device);
     if (e != hipSuccess) {
         delete p;
@@ -699,6 +719,16 @@ isoq_status kv_scores_generic(const isoq_params *pk, int dtype, const void *q, i
     return ISOQ_OK;
 }
 
+constexpr int64_t kScoreMaxLds = 160 * 1024;   // LDS of one workgroup (gfx950)
+
+// Query heads per key head past the limit that the logit calls state.
+bool group_limit(int d, int bits, int group, int m)
+{
+    const int64_t tables = bits == 4 ? d * 16 : d / 2 * (1 << 2 * bits);
+    const int64_t sketch = m ? m / 4 * 16 + m + d : 0;
+    return 4 * (group * (tables + d + sketch) + 16) > kScoreMaxLds;
+}
+
 // isoq_kv_scores and isoq_kv_scores_qjl (sk, k_signs, k_gamma non-NULL).
 isoq_status kv_scores(const isoq_params *pk, const isoq_sketch *sk, int dtype, const void *q, int n_seqs,
                       int n_q_heads, int n_kv_heads, const uint8_t *k_idx, const float *k_rho,
@@ -746,17 +776,16 @@ isoq_status kv_scores(const isoq_params *pk, const isoq_sketch *sk, int dtype, c
         return kv_scores_generic(pk, dtype, q, n_seqs, n_q_heads, n_kv_heads, k_idx, k_rho, n_blocks, block_size,
                                  block_table, max_blocks_per_seq, seq_lens, scale, scores, max_len, max_pos,
                                  stream);
-    const ScoreKernel kern = sk ? score_qjl_kernel_for(pk->variant, pk->d, pk->bits, dtype == ISOQ_F16, group, sk->m)
-                                : score_kernel_for(pk->variant, pk->d, pk->bits, dtype == ISOQ_F16, group);
+    const bool tables = score_by_tables(pk->d, pk->bits, group);
+    const ScoreKernel kern = !tables ? score_m_kernel_for(pk->d, pk->bits, group, sk ? sk->m : 0, pk->n_pass > 1)
+                             : sk    ? score_qjl_kernel_for(pk->variant, pk->d, pk->bits, dtype == ISOQ_F16, sk->m)
+                                     : score_kernel_for(pk->variant, pk->d, pk->bits, dtype == ISOQ_F16);
     if (!kern.fn)
         return ISOQ_E_UNSUPPORTED;
     const void *fn = kern.fn;
     const size_t lds = kern.dyn_lds;
-    int lds_max = 0;
-    hipError_t e = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, pk->device);
-    if (e != hipSuccess)
-        return hip_fail(e, "hipDeviceGetAttribute");
-    if (lds > (size_t)lds_max)
+    hipError_t e = hipSuccess;
+    if (lds > (size_t)kScoreMaxLds || group_limit(pk->d, pk->bits, group, sk ? sk->m : 0))
         return ISOQ_E_UNSUPPORTED;
     if (lds > 65536) {
         e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -780,9 +809,24 @@ isoq_status kv_scores(const isoq_params *pk, const isoq_sketch *sk, int dtype, c
     a.max_blocks = max_blocks_per_seq;
     a.n_sets = pk->n_sets;
     a.scale = scale;
+    a.variant = pk->variant;
+    a.q_f16 = dtype == ISOQ_F16;
     a.div_block = make_fastdiv((uint32_t)block_size);
     for (int k = 0; k < (1 << pk->bits); k++)
         a.lev_all[k] = pk->levels[k];
+    a.lv = pk->lv;
+    a.lv_more = reinterpret_cast<const LevelDigits *>(pk->dparams + pk->lv_offset);
+    a.n_pass = pk->n_pass;
+    // positions per workgroup: as many as 1,024, or 4,096 on the matrix cores
+    // with the sketch (S q is computed per workgroup, about three times the
+    // rest of its preparation: 8 x 8 x 4 heads, 32,768 keys, m = 128: 60 us at
+    // 1,024, 50 us at 2,048 and 4,096), but fewer (512 at least for the
+    // tables, whose lanes take two keys, else 256) while that leaves fewer
+    // than four workgroups (sketch: two) per compute unit
+    const int least = tables ? 512 : 256, want = sk && !tables ? 512 : 1024;
+    a.chunk = sk && !tables ? 4 * kScoreChunk : kScoreChunk;
+    while (a.chunk > least && (int64_t)n_kv_heads * n_seqs * ((max_pos + a.chunk - 1) / a.chunk) < want)
+        a.chunk /= 2;
     if (sk) {
         a.qjl_S = sk->dS;
         a.k_signs = k_signs;
@@ -790,7 +834,7 @@ isoq_status kv_scores(const isoq_params *pk, const isoq_sketch *sk, int dtype, c
         a.qjl_scale = (float)((double)scale * std::sqrt(M_PI / 2.0) / sk->m);
     }
     void *args[] = {&a};
-    const dim3 grid((unsigned)n_kv_heads, (unsigned)((max_pos + kScoreChunk - 1) / kScoreChunk), (unsigned)n_seqs);
+    const dim3 grid((unsigned)n_kv_heads, (unsigned)((max_pos + a.chunk - 1) / a.chunk), (unsigned)n_seqs);
     e = hipLaunchKernel(fn, grid, dim3(256), args, lds, static_cast<hipStream_t>(stream));
     if (e != hipSuccess)
         return hip_fail(e, "hipLaunchKernel");

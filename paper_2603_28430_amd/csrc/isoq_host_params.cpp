@@ -457,6 +457,64 @@ void build_mfma_params(int variant, int d, const float *set_layout, uint16_t *ou
 }
 
 // ------------------------------------------------------- magnitude lookup table
+void build_level_digits(int bits, const float *levels, std::vector<LevelDigits> &out)
+{
+    // magnitudes m_k of the positive half; an integer n stands for n q, or at
+    // 4 bits for (n + half) q, half = (1 + 256 + 256^2) / 2, so that the
+    // complement of n's digits, -n - 2 half, stands for -(n + half) q
+    const int H = 1 << (bits - 1);
+    const double half = bits == 4 ? 32896.5 : 0.0, top = 8355000.0;
+    double rest[8];
+    for (int k = 0; k < H; k++)
+        rest[k] = levels[H + k];
+    out.clear();
+    for (;;) {
+        double big = 0;
+        for (int k = 0; k < H; k++)
+            big = std::max(big, std::fabs(rest[k]));
+        // the quantum (a float) for which the integers come closest
+        double best = INFINITY, q = 1.0;
+        const double round = 6755399441055744.0;   // 1.5 x 2^52: adding and subtracting it rounds to an integer
+        for (int i = 0; i < 1024 && big > 0; i++) {
+            const double qi = (double)(float)(big / top * (1.0 + i / 1024.0)), inv = 1.0 / qi;
+            double err = 0;
+            for (int k = 0; k < H; k++) {
+                const double u = rest[k] * inv - half, e = (u - ((u + round) - round)) * qi;
+                err += e * e;
+            }
+            if (qi > 0 && err < best) {
+                best = err;
+                q = qi;
+            }
+        }
+        LevelDigits lv{};
+        uint8_t bytes[3][8] = {};
+        for (int k = 0; k < H; k++) {
+            const long n = std::lrint(rest[k] / q - half);
+            rest[k] -= ((double)n + half) * q;
+            for (int sign = 0; sign < (bits == 4 ? 1 : 2); sign++) {
+                long v = sign ? -n : n;
+                const int at = bits == 4 ? k : sign ? H - 1 - k : H + k;   // 4 bits: by magnitude
+                for (int t = 2; t >= 0; t--) {
+                    const long d = ((v + 128) & 255) - 128;
+                    bytes[t][at] = (uint8_t)(d & 255);
+                    v = (v - d) / 256;
+                }
+            }
+        }
+        for (int t = 0; t < 3; t++)
+            std::memcpy(lv.tab[t], bytes[t], 8);
+        // (4 bits: the query side holds digits of twice its integers)
+        lv.quantum = (float)(q * (bits == 4 ? 32768.0 : 65536.0));
+        out.push_back(lv);
+        bool done = true;
+        for (int k = 0; k < H; k++)
+            done = done && std::fabs(rest[k]) <= std::ldexp(std::fabs((double)levels[H + k]), -20);
+        if (done || out.size() == 8)
+            return;
+    }
+}
+
 bool build_magnitude_lut(int H, const double *tau, const double *lev, double *inv_h,
                          std::vector<LutEntry> &lut)
 {

@@ -111,7 +111,18 @@ struct KArgs {
     int64_t g_set_stride;      // floats per parameter set, kSlotParams * g_slots
 };
 
-// Attention logits against a paged cache of quantized keys (isoq_scores.hip).
+// The codebook as 8-bit digits for the matrix-core logit kernel
+// (isoq_scores_m.h): byte k of tab[t] is digit t (most significant first) of
+// level k's integer (4 bits: of the positive level of magnitude k), and
+// quantum the value of digit weight 256^2 in the kernel's sums.
+struct LevelDigits {
+    uint32_t tab[3][2];
+    float quantum;
+    uint32_t pad;
+};
+
+// Attention logits against a paged cache of quantized keys (isoq_scores_m.h,
+// isoq_scores_generic.hip).
 struct SArgs {
     const void *q;               // [n_seqs][n_q_heads][d] queries
     const uint8_t *k_idx;        // [n_blocks][n_kv_heads][block_size][record]
@@ -123,9 +134,14 @@ struct SArgs {
     int64_t max_len, n_blocks;
     int32_t n_q_heads, n_kv_heads, group, block_size, max_blocks, n_sets;
     float scale;
-    int32_t pad0;
+    int32_t variant, q_f16;
+    int32_t chunk;               // positions per workgroup, a multiple of 256
+    int32_t fill;                // write -inf at positions that have no key
     FastDiv div_block;
     float lev_all[16];           // c_0 .. c_{K-1}
+    LevelDigits lv;              // matrix-core kernel: the first pass over the levels' digits,
+    const LevelDigits *lv_more;  // the others (device memory)
+    int32_t n_pass;
     // stage-2 residual correction (kernels with a sketch only)
     const float *qjl_S;          // [m][d] fp32 projection
     const uint8_t *k_signs;      // [n_blocks][n_kv_heads][block_size][m/8]
@@ -134,20 +150,35 @@ struct SArgs {
     int32_t pad1;
 };
 
-// Keys per workgroup of the score kernel.
+// Keys per workgroup of the score kernels (the matrix-core kernel takes fewer
+// when that would leave compute units idle, SArgs::chunk).
 constexpr int kScoreChunk = 1024;
 
-// Score kernel for (variant, d, bits, fp16 queries?, query heads per key
-// head) and the dynamic LDS bytes it needs (0 when its LDS is static), or
-// {nullptr, 0}.
+// Whether the logits of `group` query heads per key head come from lookup
+// tables (isoq_scores.h) rather than the matrix cores (isoq_scores_m.h).  One
+// head alone does not pay for spreading a key's indices over selector bytes
+// (measured 8-40% slower than the tables at every width up to 256), except
+// where the tables need more than 64 KB of LDS (d = 512, 3 and 4 bits: 97 and
+// 121 us with tables, 30 and 40 us on the matrix cores; 4 x 16 heads, 8,192
+// keys).
+constexpr bool score_by_tables(int d, int bits, int group) { return group == 1 && !(d == 512 && bits >= 3); }
+
+// Score kernel for (variant, d, bits, fp16 queries?) with one query head per
+// key head and the dynamic LDS bytes it needs, or {nullptr, 0}.
 struct ScoreKernel {
     const void *fn;
     size_t dyn_lds;
 };
-ScoreKernel score_kernel_for(int variant, int d, int bits, bool f16, int group);
-ScoreKernel score_kernel_for_block8(int d, int bits, bool f16, int group);
+ScoreKernel score_kernel_for(int variant, int d, int bits, bool f16);
+ScoreKernel score_kernel_for_block8(int d, int bits, bool f16);
 // The same with the stage-2 residual correction of m sign bits (isoq_scores_qjl.hip).
-ScoreKernel score_qjl_kernel_for(int variant, int d, int bits, bool f16, int group, int m);
+ScoreKernel score_qjl_kernel_for(int variant, int d, int bits, bool f16, int m);
+
+// The matrix-core logit kernel (isoq_scores_m.h, any variant and query type)
+// for width d, bits, query heads per key head and m sketch bits (0: none) and
+// the dynamic LDS bytes it needs; passes: levels held in several sets of
+// digits.
+ScoreKernel score_m_kernel_for(int d, int bits, int group, int m, bool passes);
 
 // Paged caches (isoq_kv_append, isoq_kv_scores) hold a head's records of
 // one cache block piece-major: a record of R bytes is cut into pieces of
@@ -308,6 +339,10 @@ static_assert(sizeof(LutEntry) == 16, "LUT entries are 16 bytes");
 // kLutMaxCells cells would be needed.
 bool build_magnitude_lut(int H, const double *tau, const double *lev, double *inv_h,
                          std::vector<LutEntry> &lut);
+// The levels (symmetric, ascending, 2^bits of them) as digits, one set or,
+// where that leaves a level off by more than 2^-20 of itself, further sets for
+// the remainders.
+void build_level_digits(int bits, const float *levels, std::vector<LevelDigits> &out);
 // Lloyd-Max levels for N(0, sigma^2) (ascending, symmetrised).
 bool lloyd_levels(int bits, double sigma, int iters, double *levels);
 // Seeded raw draws (Philox4x32-10 + Box-Muller), layout of the public header.

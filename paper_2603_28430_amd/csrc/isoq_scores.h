@@ -1,4 +1,5 @@
-// Attention logits against a paged cache of quantized keys, for decoding.
+// Attention logits against a paged cache of quantized keys, for decoding, with
+// one query head per key head (larger groups: isoq_scores_m.h).
 //
 // A key stored by isoq_kv_append is x_hat = rho T^{-1}(c[idx]) with T the
 // block rotation of its head.  T is orthogonal (Prop. 1), so for a query q
@@ -10,11 +11,11 @@
 // bits, so a table has at most 64 entries) and field j of value e contributes
 // table[j][e] = sum_f (T q)_{F j + f} c[e_f].
 //
-// Workgroup (key head h, chunk of kScoreChunk positions, sequence s):
+// Workgroup (key head h, chunk of positions, sequence s):
 //   0. load the block-table entries of the lane's keys and the first batch
 //      of records;
-//   1. rotate the group's query heads (scale folded in) into LDS;
-//   2. build the group's tables in LDS (d/F tables of 2^(F b) floats each);
+//   1. rotate the query head (scale folded in) into LDS;
+//   2. build its tables in LDS (d/F tables of 2^(F b) floats each);
 //   3. one key per lane: its record (one load per piece of the cache
 //      layout, up to 16 bytes) and norm, the d/F
 //      lookups summed, rho * sum written.  All lanes read the same field's
@@ -62,16 +63,12 @@ struct ScoreShape {
     static constexpr int KPT = RW <= 12 ? 2 : 1;
     static constexpr int SW = QM / 32;             // sketch words per key
     static constexpr int NQ = QM / 4;              // 4-sign groups (16-entry tables) per key
-    // LDS floats for g query heads: tables, codebook, rotated queries; with
-    // the sketch also the sign tables, S q and the raw queries
-    static constexpr int lds_floats(int g) { return g * NF * E + 16 + g * D + (QM ? g * (16 * NQ + QM + D) : 0); }
+    // LDS floats: tables, codebook, rotated query; with the sketch also the
+    // sign tables, S q and the raw query.  A static array (its address is a
+    // constant the reads take as immediate offsets).
+    static constexpr int kLds = NF * E + 16 + D + (QM ? 16 * NQ + QM + D : 0);
+    static_assert(kLds * 4 <= 65536, "static LDS");
 };
-
-// A compile-time group size whose LDS fits 64 KB uses a static array (its
-// address is a constant the reads take as immediate offsets); otherwise the
-// group size comes at run time with dynamic LDS.
-template <int D, int BITS, int GT, int QM>
-constexpr bool kStaticLds = GT > 0 && ScoreShape<D, BITS, QM>::lds_floats(GT) * 4 <= 65536;
 
 // Sum of the table entries selected by the fields of one record.  `base` is
 // the LDS byte address of the query head's first table, a multiple of the
@@ -111,42 +108,31 @@ __device__ __forceinline__ float lookup_sum(const char *lds, uint32_t base, cons
     return acc[0] + acc[1];
 }
 
-// GT: query heads per key head as a compile-time constant (the table base of
-// every head then folds into the reads' immediate offsets), or 0 for any
-// group size given at run time.
-template <int VAR, int D, int BITS, bool F16, int GT, int QM>
+template <int VAR, int D, int BITS, bool F16, int QM>
 __global__ __launch_bounds__(256) void score_kernel(const SArgs a)
 {
     using S = ScoreShape<D, BITS, QM>;
     constexpr int LPQ = D / kCoordsPerLane;          // 8-coordinate chunks per query
     constexpr int PL = kLanePL<VAR>;
     constexpr int64_t RB = (int64_t)D * BITS / 8;    // record bytes
-    // LDS: tables[G][NF][E] | levels[16] | q~[G][D] | (sketch) sign tables
-    // [G][NQ][16] | S q [G][QM] | q [G][D]
-    float *smem;
-    if constexpr (kStaticLds<D, BITS, GT, QM>) {
-        __shared__ __align__(16) float sm[S::lds_floats(GT)];
-        smem = sm;
-    } else {
-        extern __shared__ __align__(16) float dyn[];
-        smem = dyn;
-    }
+    // tables[NF][E] | levels[16] | q~[D] | (sketch) sign tables [NQ][16] |
+    // S q [QM] | q [D]
+    __shared__ __align__(16) float smem[S::kLds];
     // a head's records of one cache block: block_size records of RB bytes
     const int h = (int)xcd_head(blockIdx.x, (uint32_t)a.n_kv_heads, a.block_size * RB % 128 != 0);
     const int s = blockIdx.z;
-    const int G = GT > 0 ? GT : a.group;
     int64_t len = a.seq_lens[s];
     len = min(len, a.max_len);
     len = min(len, (int64_t)a.max_blocks * a.block_size);
-    const int64_t t0 = (int64_t)blockIdx.y * kScoreChunk;
+    const int64_t t0 = (int64_t)blockIdx.y * a.chunk;
     if (t0 >= len)
         return;  // block-uniform: the whole workgroup leaves before any barrier
     float *tab = smem;
-    float *lev = tab + G * S::NF * S::E;
+    float *lev = tab + S::NF * S::E;
     float *qt = lev + 16;
-    float *tab2 = qt + G * D;
-    float *sqv = tab2 + G * 16 * S::NQ;
-    float *qraw = sqv + G * QM;
+    float *tab2 = qt + D;
+    float *sqv = tab2 + 16 * S::NQ;
+    float *qraw = sqv + QM;
     const int set = a.n_sets == 1 ? 0 : h;
 
     // 0. keys t0 + threadIdx.x + 256 i, in batches of KPT keys per lane.  A
@@ -162,7 +148,7 @@ __global__ __launch_bounds__(256) void score_kernel(const SArgs a)
     //    whole (sizes not a multiple of 8) with ordinary 2- or 4-byte loads,
     //    whose lanes are a record apart (the second and later loads of a
     //    line then hit L1).
-    const int64_t tend = min(t0 + (int64_t)kScoreChunk, len);
+    const int64_t tend = min(t0 + (int64_t)a.chunk, len);
     const int32_t *table = a.block_table + (int64_t)s * a.max_blocks;
     constexpr int NB = kScoreChunk / 256 / S::KPT;
     static_assert(NB * S::KPT * 256 == kScoreChunk, "batches tile the chunk");
@@ -248,13 +234,11 @@ __global__ __launch_bounds__(256) void score_kernel(const SArgs a)
     Batch kb[2];
     issue(0, kb[0]);
 
-    // 1. rotated queries q~_g = scale * T_h q_g and the codebook
+    // 1. rotated query q~ = scale * T_h q and the codebook
     if (threadIdx.x < S::K)
         lev[threadIdx.x] = a.lev_all[threadIdx.x];
-    for (int i = threadIdx.x; i < G * LPQ; i += blockDim.x) {
-        const int g = i / LPQ, l = i - g * LPQ;
-        const char *qrow = static_cast<const char *>(a.q) +
-                           ((int64_t)s * a.n_q_heads + (int64_t)h * G + g) * D * (F16 ? 2 : 4);
+    if (const int l = threadIdx.x; l < LPQ) {
+        const char *qrow = static_cast<const char *>(a.q) + ((int64_t)s * a.n_q_heads + h) * D * (F16 ? 2 : 4);
         Raw<F16> r;
         load_row_chunk<F16>(qrow + l * (F16 ? 16 : 32), r);
         float x[8], y[8], P[PL];
@@ -263,26 +247,25 @@ __global__ __launch_bounds__(256) void score_kernel(const SArgs a)
         rotate_forward<VAR>(P, x, y);
 #pragma unroll
         for (int k = 0; k < 8; k++)
-            qt[g * D + 8 * l + k] = y[k] * a.scale;
+            qt[8 * l + k] = y[k] * a.scale;
         if constexpr (QM > 0) {
 #pragma unroll
             for (int k = 0; k < 8; k++)
-                qraw[g * D + 8 * l + k] = x[k];
+                qraw[8 * l + k] = x[k];
         }
     }
     __syncthreads();
 
-    // 2. tables: tab[g][j][e] = sum_f q~_g[F j + f] * c[(e >> f b) mod K].
+    // 2. tables: tab[j][e] = sum_f q~[F j + f] * c[(e >> f b) mod K].
     //    A work item fills 16 consecutive entries of one table: with
     //    e = 16 m + k, the first coordinate's level index e mod K is k mod K
     //    (K <= 16 divides 16), a constant, and the second's, e >> b, takes at
     //    most two values per item.
     constexpr int EPT = S::E < 16 ? S::E : 16;
-    for (int i = threadIdx.x; i < G * S::NF * (S::E / EPT); i += blockDim.x) {
+    for (int i = threadIdx.x; i < S::NF * (S::E / EPT); i += blockDim.x) {
         const int m = i % (S::E / EPT);
-        const int gj = i / (S::E / EPT);  // g * NF + j
-        const int g = gj / S::NF, j = gj - g * S::NF;
-        const float *qg = qt + g * D + S::F * j;
+        const int j = i / (S::E / EPT);
+        const float *qg = qt + S::F * j;
         const float qa = qg[0];
         float out[EPT];
         if constexpr (S::F == 2) {
@@ -295,17 +278,16 @@ __global__ __launch_bounds__(256) void score_kernel(const SArgs a)
             for (int k = 0; k < EPT; k++)
                 out[k] = qa * a.lev_all[k];
         }
-        float4 *dst = reinterpret_cast<float4 *>(tab + (int64_t)gj * S::E + EPT * m);
+        float4 *dst = reinterpret_cast<float4 *>(tab + j * S::E + EPT * m);
 #pragma unroll
         for (int k = 0; k < EPT / 4; k++)
             dst[k] = make_float4(out[4 * k], out[4 * k + 1], out[4 * k + 2], out[4 * k + 3]);
     }
     if constexpr (QM > 0) {
-        // (S q_g)_r for every query head of the group, S fp32 [QM][D]
-        for (int i = threadIdx.x; i < G * QM; i += blockDim.x) {
-            const int g = i / QM, r = i - g * QM;
+        // (S q)_r, S fp32 [QM][D]
+        for (int r = threadIdx.x; r < QM; r += blockDim.x) {
             const float4 *srow = reinterpret_cast<const float4 *>(a.qjl_S + (int64_t)r * D);
-            const float4 *qv = reinterpret_cast<const float4 *>(qraw + g * D);
+            const float4 *qv = reinterpret_cast<const float4 *>(qraw);
             float acc = 0.f;
 #pragma unroll 8
             for (int j = 0; j < D / 4; j++) {
@@ -315,12 +297,12 @@ __global__ __launch_bounds__(256) void score_kernel(const SArgs a)
                 acc = fmaf(sv.z, q4.z, acc);
                 acc = fmaf(sv.w, q4.w, acc);
             }
-            sqv[g * QM + r] = acc * a.qjl_scale;
+            sqv[r] = acc * a.qjl_scale;
         }
         __syncthreads();
         // sign tables: entry e of group i is sum_b (bit b of e ? 1 : -1) (S q)_{4 i + b}
-        for (int i = threadIdx.x; i < G * S::NQ; i += blockDim.x) {
-            const float *v = sqv + 4 * i;  // i = g * NQ + group
+        for (int i = threadIdx.x; i < S::NQ; i += blockDim.x) {
+            const float *v = sqv + 4 * i;
             const float v0 = v[0], v1 = v[1], v2 = v[2], v3 = v[3];
             float out[16];
 #pragma unroll
@@ -337,36 +319,18 @@ __global__ __launch_bounds__(256) void score_kernel(const SArgs a)
     auto consume = [&](Batch &k) {
 #pragma unroll
         for (int u = 0; u < S::KPT; u++) {
-            float *dst = a.scores + ((int64_t)s * a.n_q_heads + (int64_t)h * G) * a.max_len + k.t[u];
-            // compile-time group sizes unroll fully; a run-time one loops
-            constexpr int GU = GT > 0 ? GT : 1;
-            for (int g0 = 0; g0 < G; g0 += GU)
-#pragma unroll
-            for (int gi = 0; gi < GU; gi++) {
-                const int g = g0 + gi;
-                // Empty asm statements keep the register footprint small: the
-                // record words look modified per query head, so the field
-                // offsets are not hoisted out of this loop (d/F registers),
-                // and the sum is complete before the branch, so the lookups
-                // are not sunk into it and held all at once.
-#pragma unroll
-                for (int c = 0; c < S::RW; c++)
-                    asm volatile("" : "+v"(k.w[u][c]));
-                const float acc = lookup_sum<S::NF, S::FB>(reinterpret_cast<const char *>(tab),
-                                                           (uint32_t)(g * S::NF * S::E * 4), k.w[u]);
-                float val = k.rho[u] * acc;
-                if constexpr (QM > 0) {
-#pragma unroll
-                    for (int c = 0; c < S::SW; c++)
-                        asm volatile("" : "+v"(k.z[u][c]));
-                    const float acc2 = lookup_sum<S::NQ, 4>(reinterpret_cast<const char *>(tab2),
-                                                             (uint32_t)(g * S::NQ * 16 * 4), k.z[u]);
-                    val = fmaf(k.gam[u], acc2, val);
-                }
-                asm volatile("" ::"v"(val));
-                if (k.ok[u])
-                    dst[(int64_t)g * a.max_len] = val;
+            float *dst = a.scores + ((int64_t)s * a.n_q_heads + h) * a.max_len + k.t[u];
+            // the sum is complete before the branch, so the lookups are not
+            // sunk into it and held all at once
+            const float acc = lookup_sum<S::NF, S::FB>(reinterpret_cast<const char *>(tab), 0u, k.w[u]);
+            float val = k.rho[u] * acc;
+            if constexpr (QM > 0) {
+                const float acc2 = lookup_sum<S::NQ, 4>(reinterpret_cast<const char *>(tab2), 0u, k.z[u]);
+                val = fmaf(k.gam[u], acc2, val);
             }
+            asm volatile("" ::"v"(val));
+            if (k.ok[u])
+                *dst = val;
         }
     };
     // 3. sums, batch by batch (the next batch's loads issued first)

@@ -4,9 +4,9 @@
 
 namespace isoq {
 
-ScoreKernel score_kernel_for_block8(int d, int bits, bool f16, int group)
+ScoreKernel score_kernel_for_block8(int d, int bits, bool f16)
 {
-    return pick_d<VAR_BLOCK8>(d, bits, f16, group);
+    return pick_d<VAR_BLOCK8>(d, bits, f16);
 }
 
 }  // namespace isoq

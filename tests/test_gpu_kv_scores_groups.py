@@ -1,0 +1,97 @@
+"""Attention logits of grouped query heads (isoq_kv_scores and
+isoq_kv_scores_qjl with two or more query heads per key head: the matrix-core
+kernel) against the oracle, at the sizes where its tiles end: every width and
+bit width, groups around its tiles of 2, 4 and 8 heads, lengths around its
+64-key batches and 256-key rounds, odd block sizes, several rounds per
+workgroup, codebooks that one set of level digits does not hold, and
+non-finite queries.
+
+Tolerances are those of test_gpu_kv_scores.py and test_gpu_kv_scores_qjl.py
+(the bound of an fp32 sum of lookups).  The digits stay inside it: a level is
+off by at most 2^-20 of itself and 2^-24 of the largest level on average, the
+query by 2^-31 of its largest coordinate, and the int32 sums are exact.
+Needs an MI355X."""
+import numpy as np
+import pytest
+
+import oracle
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_2603_28430_amd as iq  # noqa: E402
+import test_gpu_kv_scores as plain  # noqa: E402
+import test_gpu_kv_scores_qjl as sketch  # noqa: E402
+
+WIDTHS = (64, 80, 96, 128, 160, 192, 256, 512)
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("d", WIDTHS)
+@pytest.mark.parametrize("group", [2, 3])
+def test_scores_groups_widths(d, bits, group):
+    if d == 512 and bits == 3:
+        group = 2   # three heads are past the call's limit
+    run = (d // 16 + bits + group) % 4
+    plain.run_case(("full", "fast", "2d", "8d")[run], d, bits, "f16" if run % 2 else "f32", n_seqs=2, n_q=2 * group,
+                   n_kv=2, bs=(16, 7)[run // 2], seq_lens=[330, 65], seed=d + bits + group)
+
+
+@pytest.mark.parametrize("d,bits", [(128, 3), (80, 3), (192, 4), (256, 2)])
+@pytest.mark.parametrize("group", [4, 5, 8, 9])
+def test_scores_groups_tiles(d, bits, group):
+    plain.run_case("fast", d, bits, "f16", n_seqs=6, n_q=group, n_kv=1, bs=16, seq_lens=[1, 63, 64, 255, 257, 1030],
+                   max_len=1025, seed=d + group)
+
+
+def test_scores_group_single_head_wide():
+    """d = 512, 3 and 4 bits: one query head takes the matrix cores too."""
+    for bits in (3, 4):
+        plain.run_case("full", 512, bits, "f16", n_seqs=2, n_q=2, n_kv=2, bs=16, seq_lens=[700, 33], seed=bits)
+
+
+def test_scores_groups_several_rounds():
+    """Enough workgroups for 1,024 positions each (four rounds of 256 keys)."""
+    plain.run_case("fast", 64, 3, "f16", n_seqs=8, n_q=64, n_kv=32, bs=16, seq_lens=[4109] * 7 + [3000], seed=3)
+
+
+@pytest.mark.parametrize("d,m,bits,group", [(64, 64, 3, 2), (64, 128, 4, 5), (80, 128, 3, 4), (96, 64, 2, 3),
+                                            (128, 128, 3, 8), (128, 64, 4, 2), (160, 128, 2, 4), (192, 128, 4, 9),
+                                            (256, 64, 3, 4), (512, 64, 4, 1), (512, 64, 2, 2)])
+def test_scores_sketch_groups(d, m, bits, group):
+    sketch.run_case("full" if bits != 3 else "2d", d, bits, m, "f16", n_seqs=2, n_q=2 * group, n_kv=2, bs=16,
+                    seq_lens=[321, 64], seed=d + m + group)
+
+
+@pytest.mark.parametrize("bits,ratio", [(2, 3e4), (3, 1e3), (4, 200.0), (4, 40.0)])
+def test_scores_groups_wide_codebook(monkeypatch, bits, ratio):
+    """Levels spread over `ratio`: further sets of digits hold the small ones,
+    also for a key made of small levels only."""
+    k = 1 << (bits - 1)
+    pos = 0.1 * ratio ** (np.arange(k) / (k - 1) - 1.0)
+    levels = np.concatenate([-pos[::-1], pos]).astype(np.float32).astype(np.float64)
+    monkeypatch.setattr(oracle, "codebook", lambda b, d: levels)
+    plain.run_case("full", 128, bits, "f16", n_seqs=1, n_q=6, n_kv=2, bs=16, seq_lens=[300], seed=bits)
+    small = lambda s, h, n: (np.full((n, 128), k, np.uint8), np.ones(n, np.float32))  # noqa: E731
+    plain.run_case("full", 128, bits, "f32", n_seqs=1, n_q=6, n_kv=2, bs=16, seq_lens=[70], seed=bits, keys=small)
+
+
+def test_scores_groups_nonfinite_query():
+    """A query with an infinity or NaN gives NaN logits, the group's other
+    heads theirs."""
+    rng = np.random.default_rng(5)
+    p, rot, levels = plain.make("fast", 128, 3, 2)
+    cache = plain.Cache(rng, 128, 3, 1, 2, 16, [100])
+    q = rng.standard_normal((1, 8, 128)).astype(np.float32)
+    rec, rho, table, lens = cache.device()
+    ref = iq.isoq_kv_scores(p, torch.from_numpy(q).cuda(), rec, rho, table, lens, 1.0)
+    bad = q.copy()
+    bad[0, 1, 5], bad[0, 6, 127] = np.inf, np.nan
+    got = iq.isoq_kv_scores(p, torch.from_numpy(bad).cuda(), rec, rho, table, lens, 1.0)
+    for g in range(8):
+        if g in (1, 6):
+            assert torch.isnan(got[0, g, :100]).all()
+        else:
+            assert torch.equal(got[0, g], ref[0, g])
