@@ -125,10 +125,18 @@ __device__ __forceinline__ int head_exponent(float mx, int p)
 
 __device__ __forceinline__ int to_fixed(float v, int e) { return (int)__builtin_rintf(__builtin_amdgcn_ldexpf(v, e)); }
 
-// (a & mask) | (b & ~mask)
-__device__ __forceinline__ uint32_t bfi(uint32_t mask, uint32_t a, uint32_t b)
+// mask ? a : b, bit by bit, in one instruction.
+__device__ __forceinline__ uint32_t bit_select(uint32_t mask, uint32_t a, uint32_t b)
 {
     return __builtin_amdgcn_bitop3_b32(mask, a, b, 0xCA);
+}
+
+// A constant kept in a vector register: a scalar operand halves the rate of
+// the instructions that read it.
+__device__ __forceinline__ uint32_t vector_const(uint32_t k)
+{
+    asm("" : "+v"(k));
+    return k;
 }
 
 // Selector bytes of quads 4 ks .. 4 ks + n - 1 of a chunk (its words y): one
@@ -166,13 +174,13 @@ __device__ __forceinline__ void selectors(const uint32_t *y, int q0, uint32_t *s
             sel[2 * o + 1] = (x >> 4) & 0x0F0F0F0Fu;
         } else if constexpr (BITS == 3) {
             // 24 bits to the upper six bits of four bytes, two fields each
-            const uint32_t t = bfi(0xFFF00000u, x, x >> 4);
-            const uint32_t v = bfi(0xFC00FC00u, t, t >> 2);
+            const uint32_t t = bit_select(vector_const(0xFFF00000u), x, x >> 4);
+            const uint32_t v = bit_select(vector_const(0xFC00FC00u), t, t >> 2);
             sel[2 * o] = (v >> 2) & 0x07070707u;
             sel[2 * o + 1] = (v >> 5) & 0x07070707u;
         } else {
-            const uint32_t t = bfi(0x000000FFu, x, x << 8);
-            const uint32_t v = bfi(0x000F000Fu, t, t << 4);
+            const uint32_t t = bit_select(vector_const(0x000000FFu), x, x << 8);
+            const uint32_t v = bit_select(vector_const(0x000F000Fu), t, t << 4);
             sel[2 * o] = v & 0x03030303u;
             sel[2 * o + 1] = (v >> 2) & 0x03030303u;
         }
@@ -598,8 +606,8 @@ __global__ __launch_bounds__(256) void score_m_kernel(const SArgs a)
             transpose_rows(z[0], z[1], z[2], z[3]);
 #pragma unroll
             for (int c = 0; c < 4; c++) {
-                const uint32_t t = bfi(0x000000FFu, z[c], z[c] << 8);
-                z[c] = bfi(0x000F000Fu, t, t << 4);
+                const uint32_t t = bit_select(vector_const(0x000000FFu), z[c], z[c] << 8);
+                z[c] = bit_select(vector_const(0x000F000Fu), t, t << 4);
             }
         }
         // the batch is in y and z: the next one's loads go out now
