@@ -1079,10 +1079,12 @@ isoq_status isoq_quantize_qjl(const isoq_params *p, const isoq_sketch *sk, int d
     const int64_t tiles = (n + rpb - 1) / rpb;
     if (tiles > 0x7FFFFFFF)
         return ISOQ_E_UNSUPPORTED;
-    // with one rotation set, blocks walk several tiles each (the projection is
+    // the matrix-core encoder takes one block per tile; on the VALU encoder
+    // blocks walk several tiles each with one rotation set (the projection is
     // staged once per block; kQjlBlocks 4-wave blocks or half as many 8-wave
-    // ones); otherwise one block per tile keeps each block on its own set
-    const int64_t blocks = p->n_sets == 1 ? std::min<int64_t>(tiles, kQjlBlocks * 4 / waves) : tiles;
+    // ones), and one per tile keeps each block on its own set otherwise
+    const bool quad = dtype == ISOQ_F16 && quad_layout(p->variant, p->d, p->bits);
+    const int64_t blocks = p->n_sets == 1 && !quad ? std::min<int64_t>(tiles, kQjlBlocks * 4 / waves) : tiles;
     KArgs a{};
     fill_args(p, a);
     a.x = x;
@@ -1162,14 +1164,20 @@ isoq_status isoq_kv_append_qjl(const isoq_params *pk, const isoq_sketch *sk, int
     const void *fn = qjl_kernel_for(pk->variant, pk->d, pk->bits, dtype == ISOQ_F16, sk->m, true, waves);
     if (!fn)
         return ISOQ_E_UNSUPPORTED;
-    // block (x, y) = (head, token range); a block stages its head's projection
-    // once and walks token ranges y, y + gridDim.y, ... of that head
     const int64_t rpr = rows_per_block(pk) / 4 * waves;   // tokens per range
     const int64_t ranges = (n_tokens + rpr - 1) / rpr;
+    void *args[] = {&a};
+    if (dtype == ISOQ_F16 && quad_layout(pk->variant, pk->d, pk->bits)) {
+        // matrix-core encoder: block (x, z, y) = (head, token range)
+        const unsigned by = (unsigned)std::min<int64_t>(ranges, 65535), bz = (unsigned)((ranges + by - 1) / by);
+        return launch(fn, dim3((unsigned)n_heads, by, bz), args, stream, 64 * waves);
+    }
+    // VALU encoder: block (x, y) = (head, token range); a block stages its
+    // head's projection once and walks token ranges y, y + gridDim.y, ... of
+    // that head
     const int64_t by = std::max<int64_t>(1, std::min<int64_t>(ranges, kQjlBlocks * 4 / waves / n_heads));
     if (by > 65535)
         return ISOQ_E_UNSUPPORTED;
-    void *args[] = {&a};
     return launch(fn, dim3((unsigned)n_heads, (unsigned)by, 1), args, stream, 64 * waves);
 }
 

@@ -2,12 +2,12 @@
 // isoq_stage1m.h (fp16 rows) or isoq_stage1.h (fp32 rows) in MODE_QJL (rows
 // in, rows out) or MODE_APPEND_QJL (token rows into the slots of a paged
 // cache), which also writes sign(S (x - x_hat)) as m bits and ||x - x_hat||
-// per row.  The projection is the path's one dense contraction, P = E S'^T over a wave's tile of rows, on MFMA (fp16 inputs,
-// fp32 accumulation); S' = S T^{-1} per rotation set is staged in LDS once
-// per block.  Blocks have 8 waves, or 4 for quantize with several sets
-// (WAVES, chosen by qjl_waves): at d = 128, m = 128 the staged projection
-// (32 KB) and the waves' error tiles let three 4-wave blocks (12 waves) or
-// two 8-wave blocks (16 waves) share a CU's LDS.
+// per row.  The projection is the path's one dense contraction, P = E S'^T over a
+// tile of rows, on MFMA (fp16 inputs, fp32 accumulation).  On the matrix-core
+// encoder a block's waves project its rows together, each with its part of
+// S' = S T^{-1} in registers (isoq_stage1m.h); on the VALU encoder each wave
+// projects its own rows and S' is staged in LDS once per block.  Blocks have 8
+// waves, or 4 for quantize with several sets (WAVES, chosen by qjl_waves).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -28,15 +28,16 @@ __global__ __launch_bounds__(WAVES * 64) void qjl_kernel(const KArgs a)
 {
     using S = Stage1<VAR, D, BITS, F16, MODE, false, QM, WAVES>;
     __shared__ __align__(16) LutEntry lds_lut[S::kUseLut ? kLutMaxCells : 1];
-    __shared__ __align__(16) _Float16 lds_frag[QM * D];
     if constexpr (F16 && quad_layout(VAR, D, BITS)) {
         using M = Stage1M<VAR, D, BITS, MODE, QM, WAVES>;
-        static_assert(M::kTileRows == S::kTileRows, "the two layouts tile rows alike");
+        static_assert(M::kBlockRows == WAVES * S::kTileRows, "the two layouts tile rows alike");
         __shared__ __align__(16) u32x4 lds_par[M::kLdsWords];
-        __shared__ __align__(16) _Float16 lds_e[WAVES * M::kTileRows * M::kEStride];
-        __shared__ int64_t lds_crow[MODE == MODE_APPEND_QJL ? WAVES * M::kTileRows : 1];
-        M::run(a, lds_lut, lds_par, lds_frag, lds_e, lds_crow);
+        __shared__ __align__(16) _Float16 lds_e[M::kBlockRows * M::kEStride];
+        __shared__ uint32_t lds_sign[M::kBlockRows * M::kSignWords];
+        __shared__ int64_t lds_crow[MODE == MODE_APPEND_QJL ? M::kBlockRows : 1];
+        M::run(a, lds_lut, lds_par, lds_e, lds_sign, lds_crow);
     } else {
+        __shared__ __align__(16) _Float16 lds_frag[QM * D];
         __shared__ float lds_levels[16];
         __shared__ __align__(16) float lds_params[S::LPV * S::PL];
         __shared__ __align__(16) _Float16 lds_e[WAVES * S::kTileRows * S::kEStride];

@@ -51,6 +51,7 @@ namespace {
 
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef float f32x4m __attribute__((ext_vector_type(4)));
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 
 constexpr int DPP_ROW_SHL4 = 0x104;   // lane i reads lane i + 4 of its 16-lane row
 constexpr int DPP_ROW_ROR4 = 0x124;   // lane i reads lane i - 4 (mod 16) of its row
@@ -95,8 +96,11 @@ struct Stage1M {
     static constexpr bool kAppend = MODE == MODE_APPEND || MODE == MODE_APPEND_QJL;
     static constexpr bool kRoundtrip = MODE == MODE_ROUNDTRIP;
     static constexpr bool kEncode = !kRoundtrip;
-    static constexpr int kTileRows = RT;
-    static constexpr int kEStride = D;   // unpadded, chunk positions swizzled (err_swizzle)
+    // stage-2 sketch: rows of the block's error tile in LDS (unpadded, chunk
+    // positions swizzled: err_swizzle), their sign records beside it
+    static constexpr int kBlockRows = WAVES * RT;
+    static constexpr int kEStride = D;
+    static constexpr int kSignWords = QM > 0 ? QM / 32 : 1;
     static_assert(quad_layout(VAR, D, BITS), "quad layout variants and widths");
     static_assert(MODE != MODE_DEQUANTIZE, "the decoder keeps the VALU layout");
     static_assert(kTileGroups % SPQ == 0, "a row quad's loads fit in a tile");
@@ -111,19 +115,13 @@ struct Stage1M {
     static constexpr bool kEarly = !kQjl;
 
     // Geometry of load u for the lane of MFMA block b (= lane / 4) in wave w:
-    // its chunk, its quad in the wave's tile and its quad in the block's tile
-    // (block quad q holds block-tile rows 4 q .. 4 q + 3; the waves' loads u
-    // together cover consecutive quads).
+    // its chunk and its quad in the block's tile (block quad q holds
+    // block-tile rows 4 q .. 4 q + 3; the waves' loads u together cover
+    // consecutive quads).
     __device__ static __forceinline__ int chunk_of(int u, int b) { return C <= 16 ? b % C : 16 * (u % SPQ) + b; }
-    __device__ static __forceinline__ int wquad_of(int u, int b) { return C <= 16 ? QPS * u + b / C : u / SPQ; }
     __device__ static __forceinline__ int bquad_of(int u, int b, int w)
     {
         return C <= 16 ? (WAVES * u + w) * QPS + b / C : WAVES * (u / SPQ) + w;
-    }
-    // block quad of wave quad wq (the inverse of wquad_of, for the sketch)
-    __device__ static __forceinline__ int bquad_of_wquad(int wq, int w)
-    {
-        return C <= 16 ? (WAVES * (wq / QPS) + w) * QPS + wq % QPS : WAVES * wq + w;
     }
 
     struct In {
@@ -273,21 +271,24 @@ struct Stage1M {
     static constexpr int kLdsP = kStage && kRoundtrip ? PL / 4 * C : 0;  // 16-byte words
     static constexpr int kLdsWords = kLdsA + kLdsP > 0 ? kLdsA + kLdsP : 1;
 
-    __device__ static void run(const KArgs &a, LutEntry *lds_lut, u32x4 *lds_par, _Float16 *lds_frag = nullptr,
-                               _Float16 *lds_e = nullptr, int64_t *lds_crow = nullptr)
+    __device__ static void run(const KArgs &a, LutEntry *lds_lut, u32x4 *lds_par, _Float16 *lds_e = nullptr,
+                               uint32_t *lds_sign = nullptr, int64_t *lds_crow = nullptr)
     {
         constexpr int BT = WAVES * 64;
         const int lane = threadIdx.x & 63;
         const int b = lane >> 2, qi = lane & 3;
         const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        const int64_t tile0 = kByHead ? blockIdx.y : blockIdx.x;
+        // (append with the sketch: the grid's y and z together, so that any
+        // number of token ranges fits)
+        const int64_t tile0 = kQjl && kAppend ? (int64_t)blockIdx.z * gridDim.y + blockIdx.y
+                              : kByHead       ? (int64_t)blockIdx.y
+                                              : (int64_t)blockIdx.x;
         const int64_t rows_per_tile = (int64_t)WAVES * RT;
         // rows of the block's sequence: all rows, the tokens (append), or the
         // rows of stream blockIdx.x
         const int64_t nrows = STREAMS ? (a.n - blockIdx.x + a.n_sets - 1) / a.n_sets : a.n;
 
-        // 1. block-wide tables: the 4-bit lookup table and the sketch's
-        //    projection of the block's set, staged through LDS
+        // 1. block-wide tables: the 4-bit lookup table, staged through LDS
         if constexpr (kUseLut) {
             const u32x4 *s4 = reinterpret_cast<const u32x4 *>(a.lut);
             u32x4 *d4 = reinterpret_cast<u32x4 *>(lds_lut);
@@ -300,10 +301,8 @@ struct Stage1M {
                             : kByHead   ? (int64_t)blockIdx.x
                                         : (tile0 * rows_per_tile / a.rows_per_set) % a.n_sets;
         if constexpr (kQjl) {
-            const u32x4 *f4 = reinterpret_cast<const u32x4 *>(a.qjl_frag + set * (int64_t)(QM * D));
-            u32x4 *g4 = reinterpret_cast<u32x4 *>(lds_frag);
-            for (int i = threadIdx.x; i < QM * D / 8; i += BT)
-                g4[i] = f4[i];
+            for (int i = threadIdx.x; i < kBlockRows * kSignWords; i += BT)
+                lds_sign[i] = 0u;
         }
         if constexpr (kStage) {
             // the set's matrix pieces ([chunk][quad row][piece] in memory)
@@ -321,7 +320,7 @@ struct Stage1M {
                 }
             }
         }
-        if constexpr (kStage || kUseLut || kQjl)
+        if constexpr (kStage || kUseLut)   // (the sketch's first tile has a barrier of its own)
             __syncthreads();
 
         // 2. the lane's matrix rows (quad row qi) of its SPQ chunks (the
@@ -350,32 +349,38 @@ struct Stage1M {
         for (int k = 0; k < H - 1; k++)
             thr[k] = a.thr_pos[k];
 
-        // 3. tiles: one per block, or with the sketch a stride of them (the
-        //    staged projection then serves several).  A wave whose first row
-        //    is past the end has nothing left.
-        _Float16 *eq = kQjl ? lds_e + w * RT * kEStride : nullptr;
-        // append with the sketch: the cache row of each tile row (-1: a
-        // skipped slot), written by the encoder and read by the sketch
-        int64_t *crq = kQjl && kAppend ? lds_crow + w * RT : nullptr;
-        const int64_t tstride = kQjl ? (int64_t)(kAppend ? gridDim.y : gridDim.x) : (int64_t)1 << 40;
+        // 3. tiles.  A wave whose first row is past the end has nothing to do.
         const int64_t first_quad = C <= 16 ? (int64_t)w * QPS : w;   // bquad_of(0, 0, w)
         In buf[kTileGroups];
         int roffs[kTileGroups];   // the lane's row in the tile, per load (quad order)
-        for (int64_t tb = tile0;; tb += tstride) {
-            const int64_t row0 = tb * rows_per_tile;
+        if constexpr (kQjl) {
+            // encode (errors to LDS), project together, write the signs
+            const int64_t row0 = tile0 * rows_per_tile;
+            __syncthreads();   // the cleared sign records
+            if (row0 + rows_per_tile <= nrows) {
+                load<false>(a, row0, nrows, b, qi, w, buf, roffs);
+                process<false>(a, Am, lds_par, lev, thr, lds_lut, row0, nrows, b, qi, w, lds_e, lds_crow, buf, roffs);
+            } else if (row0 + 4 * first_quad < nrows) {
+                load<true>(a, row0, nrows, b, qi, w, buf, roffs);
+                process<true>(a, Am, lds_par, lev, thr, lds_lut, row0, nrows, b, qi, w, lds_e, lds_crow, buf, roffs);
+            }
+            half8 F[kTilesPerWave][D / 32];
+            load_projection(a, set, w, F);
+            __syncthreads();
+            project(F, lds_e, lds_sign, w);
+            __syncthreads();
+            write_signs(a, lds_sign, lds_crow, row0, nrows, w);
+        } else {
+            const int64_t row0 = tile0 * rows_per_tile;   // one tile per block
             if (row0 + 4 * first_quad >= nrows)
                 return;
             if (row0 + rows_per_tile <= nrows) {
                 load<false>(a, row0, nrows, b, qi, w, buf, roffs);
-                process<false>(a, Am, lds_par, lev, thr, lds_lut, row0, nrows, b, qi, w, eq, crq, buf, roffs);
+                process<false>(a, Am, lds_par, lev, thr, lds_lut, row0, nrows, b, qi, w, nullptr, nullptr, buf, roffs);
             } else {
                 load<true>(a, row0, nrows, b, qi, w, buf, roffs);
-                process<true>(a, Am, lds_par, lev, thr, lds_lut, row0, nrows, b, qi, w, eq, crq, buf, roffs);
+                process<true>(a, Am, lds_par, lev, thr, lds_lut, row0, nrows, b, qi, w, nullptr, nullptr, buf, roffs);
             }
-            if constexpr (kQjl)
-                sketch(a, lds_frag, eq, crq, row0, w);
-            else
-                return;
         }
     }
 
@@ -457,7 +462,10 @@ struct Stage1M {
                 if constexpr (!kEarly)
                     rotate(Am[h], buf[u0 + h].raw, ylate);
                 e2[h] = compute(a, lds_par, lev, thr, lut, buf[u0 + h], row0, roffs[u0 + h],
-                                chunk_of(u0 + h, b), rho, rho_e, eq, 4 * wquad_of(u0 + h, b) + qi,
+                                chunk_of(u0 + h, b), rho, rho_e, eq,
+                                // the row of the error tile (a constant step
+                                // per load; at d = 256 that form cost 10%)
+                                C <= 16 ? 4 * bquad_of(u0 + h, b, w) + qi : roffs[u0 + h],
                                 kEarly ? yy[u0 + h] : ylate, rl, row_chunk_of(u0 + h, lane), crq, crow);
             }
             if constexpr (kQjl) {
@@ -469,6 +477,9 @@ struct Stage1M {
                 const float gamma = rho * __builtin_amdgcn_sqrtf(s2);
                 if (chunk_of(u0, b) == 0)   // the lane of the row's chunk 0
                     emit_gamma(a, row0 + roffs[u0], crow, gamma);
+                // one row quad at a time (interleaved, they take more
+                // registers than the occupancy is worth)
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
     }
@@ -521,7 +532,12 @@ struct Stage1M {
                 float lvs[H];
 #pragma unroll
                 for (int k = 0; k < H; k++)
-                    lvs[k] = lev[k] * lscale;
+                    lvs[k] = lev[k];
+                if (__builtin_amdgcn_ballot_w64(rho == 0.f) != 0) {   // rare, and the same for the whole wave
+#pragma unroll
+                    for (int k = 0; k < H; k++)
+                        lvs[k] *= lscale;
+                }
                 p = ballot_encode<BITS, kQjl>(y, m, ths, lvs, yq);
             } else {
                 p = ballot_encode<BITS, kQjl>(y, m, ths, lev, yq);
@@ -580,12 +596,12 @@ struct Stage1M {
         float s2 = 0.f;
         if constexpr (kQjl) {
             // e = y / rho' - c[idx], the normalised rotated-domain error (zero
-            // for a zero row), to the wave's LDS tile as fp16
+            // for a zero row); -e to the block's LDS tile as fp16
             const float inv = __builtin_amdgcn_rcpf(rho_e);
             float e[8];
 #pragma unroll
             for (int j = 0; j < 8; j++) {
-                e[j] = fmaf(y[j], inv, -yq[j]);
+                e[j] = fmaf(-y[j], inv, yq[j]);
                 s2 = fmaf(e[j], e[j], s2);
             }
             u32x4 hv;
@@ -600,23 +616,105 @@ struct Stage1M {
         return s2;
     }
 
-    // Stage-2 sketch of the wave's tile: tile row 4 wq + i is row i of the
-    // wave's quad wq.
-    __device__ static __forceinline__ void sketch(const KArgs &a, const _Float16 *frag, const _Float16 *eq,
-                                                  const int64_t *crq, int64_t row0, int w)
+    // ---- stage-2 sketch ------------------------------------------------------------
+    // One tile of kBlockRows rows per block, whose errors E (LDS) all waves
+    // project together: wave w loads the 16 rows of S' of column tile w mod NT
+    // into registers and takes every row block of 16 (m = 64: every second
+    // one), so S' needs no LDS and the block's only LDS is E and the signs
+    // (34 KB at d = m = 128).  The kernel is bound by VALU issue (about 165
+    // instructions per 4 rows at 3 bits) and the matrix instructions that
+    // share it.  With S' staged in LDS, blocks walked several tiles (to stage
+    // it less often), which took 110 registers and held a CU to two blocks of
+    // eight waves; a block of one tile takes 54.  Measured at d = 128, m =
+    // 128, 3 bits: 1,000,003 rows 108.4 -> 106.6 us, append of 8 x 4,096
+    // tokens x 32 heads 125.9 -> 117.9 us; d = 64 quantize 5% less, d = 256
+    // quantize 5% and append 8% less.  The products are those of qjl_project
+    // (k steps in order, fp32 accumulation), with the errors negated: the sign
+    // bit of a result is the sketch bit.
+    static constexpr int NT = QM / 16 > 0 ? QM / 16 : 1;              // column tiles of S'
+    static constexpr int kTilesPerWave = NT > WAVES ? NT / WAVES : 1;  // a wave's: w mod NT, + WAVES, ...
+    static constexpr int kWavesPerTile = WAVES > NT ? WAVES / NT : 1;  // which share its row blocks
+
+    __device__ static __forceinline__ void load_projection(const KArgs &a, int64_t set, int w,
+                                                           half8 (*F)[D / 32])
     {
-        qjl_project<D, QM, kTileRows, kEStride, true>(frag, eq, [&](int ar) -> uint32_t * {
-            const int64_t row = row0 + 4 * bquad_of_wquad(ar >> 2, w) + (ar & 3);
-            if (ar >= kTileRows || row >= a.n)
-                return nullptr;
-            int64_t orow = row;
-            if constexpr (kAppend) {
-                orow = crq[ar];   // the encoder's cache row of tile row ar
-                if (orow < 0)
-                    return nullptr;
+        // an offset the compiler cannot see through (it is zero): the loads
+        // stay in the tile loop
+        int o = 0;
+        asm volatile("" : "+s"(o));
+#pragma unroll
+        for (int t = 0; t < kTilesPerWave; t++) {
+            const half8 *f = o + reinterpret_cast<const half8 *>(a.qjl_frag + set * (int64_t)(QM * D)) +
+                             (w % NT + t * WAVES) * (D / 32) * 64 + (threadIdx.x & 63);
+#pragma unroll
+            for (int ks = 0; ks < D / 32; ks++)
+                F[t][ks] = f[ks * 64];
+        }
+    }
+
+    __device__ static __forceinline__ void project(const half8 (*F)[D / 32], const _Float16 *e, uint32_t *sign, int w)
+    {
+        constexpr int RBS = kWavesPerTile, RB = kBlockRows / 16;   // row blocks of 16
+        static_assert(RB % (2 * RBS) == 0, "row blocks in pairs");
+        const int l = threadIdx.x & 63, r16 = l & 15, kq = l >> 4;
+        const int swz = err_swizzle(r16);
+        // two row blocks at a time (independent accumulations)
+#pragma unroll 1
+        for (int rb = w / NT; rb < RB; rb += 2 * RBS) {
+            const _Float16 *e0 = e + (16 * rb + r16) * kEStride, *e1 = e0 + 16 * RBS * kEStride;
+            f32x4m acc0[kTilesPerWave], acc1[kTilesPerWave];
+#pragma unroll
+            for (int t = 0; t < kTilesPerWave; t++)
+                acc0[t] = acc1[t] = f32x4m{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < D / 32; ks++) {
+                const int pos = 8 * ((4 * ks + kq) ^ swz);
+                const half8 E0 = *reinterpret_cast<const half8 *>(e0 + pos);
+                const half8 E1 = *reinterpret_cast<const half8 *>(e1 + pos);
+#pragma unroll
+                for (int t = 0; t < kTilesPerWave; t++) {
+                    acc0[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(F[t][ks], E0, acc0[t], 0, 0, 0);
+                    acc1[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(F[t][ks], E1, acc1[t], 0, 0, 0);
+                }
             }
-            return reinterpret_cast<uint32_t *>(a.qjl_signs + orow * (QM / 8));
-        });
+            // bits 4 nt .. 4 nt + 3 of part kq (m / 4 bits) of row 16 rb + r16
+            auto put = [&](int r, int nt, const f32x4m &acc) {
+                uint32_t p = 0;
+#pragma unroll
+                for (int i = 3; i >= 0; i--)
+                    p = __builtin_amdgcn_alignbit(p, __float_as_uint(acc[i]), 31);
+                const int bit = QM / 4 * kq + 4 * nt;
+                atomicOr(sign + r * kSignWords + bit / 32, p << (bit % 32));
+            };
+#pragma unroll
+            for (int t = 0; t < kTilesPerWave; t++) {
+                put(16 * rb + r16, w % NT + t * WAVES, acc0[t]);
+                put(16 * (rb + RBS) + r16, w % NT + t * WAVES, acc1[t]);
+            }
+        }
+    }
+
+    // The signs of the wave's share of the block's rows (consecutive rows),
+    // cleared for the next tile.
+    __device__ static __forceinline__ void write_signs(const KArgs &a, uint32_t *sign, const int64_t *crow, int64_t row0,
+                                                       int64_t nrows, int w)
+    {
+        const int lane = threadIdx.x & 63;
+#pragma unroll
+        for (int i0 = 0; i0 < RT * kSignWords; i0 += 64) {
+            const int i = i0 + lane, r = w * RT + i / kSignWords, wd = i % kSignWords;
+            if (i < RT * kSignWords) {
+                const uint32_t v = sign[r * kSignWords + wd];
+                sign[r * kSignWords + wd] = 0u;
+                if (row0 + r < nrows) {
+                    int64_t orow = row0 + r;
+                    if constexpr (kAppend)
+                        orow = crow[r];   // the encoder's cache row (-1: a skipped slot)
+                    if (!kAppend || orow >= 0)
+                        reinterpret_cast<uint32_t *>(a.qjl_signs + orow * (QM / 8))[wd] = v;
+                }
+            }
+        }
     }
 };
 
