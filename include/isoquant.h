@@ -345,6 +345,21 @@ isoq_status isoq_kv_scores_qjl(const isoq_params *pk, const isoq_sketch *sk, int
                                int max_blocks_per_seq, const int32_t *seq_lens, float scale, float *scores,
                                int64_t max_len, void *stream);
 
+/*
+ * isoq_kv_scores_filled -- isoq_kv_scores (sk, k_signs and k_gamma NULL) or
+ * isoq_kv_scores_qjl that also writes -inf to every position of
+ * scores[s][hq][0 .. max_len) which those leave unwritten, so that a softmax
+ * over max_len ignores them and the buffer needs no initialisation.
+ * n_blocks and max_blocks_per_seq may be 0 (every position is then -inf);
+ * max_len at most 67,107,840.
+ */
+isoq_status isoq_kv_scores_filled(const isoq_params *pk, const isoq_sketch *sk, int dtype, const void *q,
+                                  int n_seqs, int n_q_heads, int n_kv_heads, const uint8_t *k_idx,
+                                  const float *k_rho, const uint8_t *k_signs, const float *k_gamma,
+                                  int64_t n_blocks, int block_size, const int32_t *block_table,
+                                  int max_blocks_per_seq, const int32_t *seq_lens, float scale, float *scores,
+                                  int64_t max_len, void *stream);
+
 /* Sizes: bytes of one packed index record, ceil(pw * bits / 8) with the
  * padded width pw = 4 g4 (Full, Fast) or 2 g2 (2-D); isoq_packed_bytes is
  * ceil(d * bits / 8), the same number whenever d is a multiple of 4.  Raw

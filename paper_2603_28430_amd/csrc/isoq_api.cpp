@@ -675,7 +675,7 @@ isoq_status kv_scores_generic(const isoq_params *pk, int dtype, const void *q, i
                               int n_kv_heads, const uint8_t *k_idx, const float *k_rho, int64_t n_blocks,
                               int block_size, const int32_t *block_table, int max_blocks_per_seq,
                               const int32_t *seq_lens, float scale, float *scores, int64_t max_len,
-                              int64_t max_pos, void *stream)
+                              int64_t max_pos, bool fill, void *stream)
 {
     const void *fn = generic_score_kernel_for(pk->variant, pk->bits, dtype == ISOQ_F16);
     if (!fn)
@@ -704,6 +704,7 @@ isoq_status kv_scores_generic(const isoq_params *pk, int dtype, const void *q, i
     a.max_blocks = max_blocks_per_seq;
     a.n_sets = pk->n_sets;
     a.scale = scale;
+    a.fill = fill;
     a.div_block = make_fastdiv((uint32_t)block_size);
     for (int k = 0; k < (1 << pk->bits); k++)
         a.lev_all[k] = pk->levels[k];
@@ -729,12 +730,13 @@ bool group_limit(int d, int bits, int group, int m)
     return 4 * (group * (tables + d + sketch) + 16) > kScoreMaxLds;
 }
 
-// isoq_kv_scores and isoq_kv_scores_qjl (sk, k_signs, k_gamma non-NULL).
+// isoq_kv_scores and isoq_kv_scores_qjl (sk, k_signs, k_gamma non-NULL), and
+// with fill isoq_kv_scores_filled.
 isoq_status kv_scores(const isoq_params *pk, const isoq_sketch *sk, int dtype, const void *q, int n_seqs,
                       int n_q_heads, int n_kv_heads, const uint8_t *k_idx, const float *k_rho,
                       const uint8_t *k_signs, const float *k_gamma, int64_t n_blocks, int block_size,
                       const int32_t *block_table, int max_blocks_per_seq, const int32_t *seq_lens, float scale,
-                      float *scores, int64_t max_len, void *stream)
+                      float *scores, int64_t max_len, bool fill, void *stream)
 {
     if (!pk)
         return ISOQ_E_NULL;
@@ -753,16 +755,19 @@ isoq_status kv_scores(const isoq_params *pk, const isoq_sketch *sk, int dtype, c
     const bool generic = !decode_d(pk->d);
     if (generic && sk)
         return ISOQ_E_UNSUPPORTED;
-    const int64_t max_pos = std::min<int64_t>(max_len, (int64_t)max_blocks_per_seq * block_size);
+    const bool no_keys = n_blocks == 0 || max_blocks_per_seq == 0;
+    const int64_t max_pos = fill ? max_len : std::min<int64_t>(max_len, (int64_t)max_blocks_per_seq * block_size);
     if (n_seqs > 65535 || (int64_t)max_blocks_per_seq * block_size > 0x7FFFFFFF ||
         (max_pos + kScoreChunk - 1) / kScoreChunk > 65535)
         return ISOQ_E_UNSUPPORTED;
-    if (n_seqs == 0 || max_pos == 0 || n_blocks == 0)
+    if (n_seqs == 0 || max_pos == 0 || (n_blocks == 0 && !fill))
         return ISOQ_OK;
-    if (!q || !k_idx || !k_rho || !block_table || !seq_lens || !scores)
+    if (!q || !seq_lens || !scores || (!(fill && no_keys) && (!k_idx || !k_rho || !block_table)))
         return ISOQ_E_NULL;
-    if (sk && (!k_signs || !k_gamma))
+    if (sk && !(fill && no_keys) && (!k_signs || !k_gamma))
         return ISOQ_E_NULL;
+    if (no_keys)
+        max_blocks_per_seq = 0;   // every sequence is then empty: the kernels only fill
     if (!aligned(q, 16) || !aligned(k_idx, 16) || !aligned(k_rho, 4) || !aligned(block_table, 4) ||
         !aligned(seq_lens, 4) || !aligned(scores, 4))
         return ISOQ_E_ALIGN;
@@ -775,7 +780,7 @@ isoq_status kv_scores(const isoq_params *pk, const isoq_sketch *sk, int dtype, c
     if (generic)
         return kv_scores_generic(pk, dtype, q, n_seqs, n_q_heads, n_kv_heads, k_idx, k_rho, n_blocks, block_size,
                                  block_table, max_blocks_per_seq, seq_lens, scale, scores, max_len, max_pos,
-                                 stream);
+                                 fill, stream);
     const bool tables = score_by_tables(pk->d, pk->bits, group);
     const ScoreKernel kern = !tables ? score_m_kernel_for(pk->d, pk->bits, group, sk ? sk->m : 0, pk->n_pass > 1)
                              : sk    ? score_qjl_kernel_for(pk->variant, pk->d, pk->bits, dtype == ISOQ_F16, sk->m)
@@ -811,6 +816,7 @@ isoq_status kv_scores(const isoq_params *pk, const isoq_sketch *sk, int dtype, c
     a.scale = scale;
     a.variant = pk->variant;
     a.q_f16 = dtype == ISOQ_F16;
+    a.fill = fill;
     a.div_block = make_fastdiv((uint32_t)block_size);
     for (int k = 0; k < (1 << pk->bits); k++)
         a.lev_all[k] = pk->levels[k];
@@ -856,7 +862,18 @@ isoq_status isoq_kv_scores(const isoq_params *pk, int dtype, const void *q, int 
 {
     return kv_scores(pk, nullptr, dtype, q, n_seqs, n_q_heads, n_kv_heads, k_idx, k_rho, nullptr, nullptr,
                      n_blocks, block_size, block_table, max_blocks_per_seq, seq_lens, scale, scores, max_len,
-                     stream);
+                     false, stream);
+}
+
+isoq_status isoq_kv_scores_filled(const isoq_params *pk, const isoq_sketch *sk, int dtype, const void *q,
+                                  int n_seqs, int n_q_heads, int n_kv_heads, const uint8_t *k_idx,
+                                  const float *k_rho, const uint8_t *k_signs, const float *k_gamma,
+                                  int64_t n_blocks, int block_size, const int32_t *block_table,
+                                  int max_blocks_per_seq, const int32_t *seq_lens, float scale, float *scores,
+                                  int64_t max_len, void *stream)
+{
+    return kv_scores(pk, sk, dtype, q, n_seqs, n_q_heads, n_kv_heads, k_idx, k_rho, k_signs, k_gamma, n_blocks,
+                     block_size, block_table, max_blocks_per_seq, seq_lens, scale, scores, max_len, true, stream);
 }
 
 isoq_status isoq_kv_scores_qjl(const isoq_params *pk, const isoq_sketch *sk, int dtype, const void *q,
@@ -869,7 +886,7 @@ isoq_status isoq_kv_scores_qjl(const isoq_params *pk, const isoq_sketch *sk, int
     if (!sk)
         return ISOQ_E_NULL;
     return kv_scores(pk, sk, dtype, q, n_seqs, n_q_heads, n_kv_heads, k_idx, k_rho, k_signs, k_gamma, n_blocks,
-                     block_size, block_table, max_blocks_per_seq, seq_lens, scale, scores, max_len, stream);
+                     block_size, block_table, max_blocks_per_seq, seq_lens, scale, scores, max_len, false, stream);
 }
 
 isoq_status isoq_sketch_init(isoq_sketch **out, const isoq_params *p, int m, const double *S_host,

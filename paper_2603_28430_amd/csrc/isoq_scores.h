@@ -125,8 +125,14 @@ __global__ __launch_bounds__(256) void score_kernel(const SArgs a)
     len = min(len, a.max_len);
     len = min(len, (int64_t)a.max_blocks * a.block_size);
     const int64_t t0 = (int64_t)blockIdx.y * a.chunk;
-    if (t0 >= len)
-        return;  // block-uniform: the whole workgroup leaves before any barrier
+    // positions below tfill without a key get -inf (none unless asked for)
+    const int64_t tfill = a.fill ? min(t0 + (int64_t)a.chunk, a.max_len) : 0;
+    float *const out = a.scores + ((int64_t)s * a.n_q_heads + h) * a.max_len;
+    if (t0 >= len) {  // block-uniform: the whole workgroup leaves before any barrier
+        for (int64_t t = t0 + threadIdx.x; t < tfill; t += 256)
+            out[t] = -INFINITY;
+        return;
+    }
     float *tab = smem;
     float *lev = tab + S::NF * S::E;
     float *qt = lev + 16;
@@ -319,7 +325,6 @@ __global__ __launch_bounds__(256) void score_kernel(const SArgs a)
     auto consume = [&](Batch &k) {
 #pragma unroll
         for (int u = 0; u < S::KPT; u++) {
-            float *dst = a.scores + ((int64_t)s * a.n_q_heads + h) * a.max_len + k.t[u];
             // the sum is complete before the branch, so the lookups are not
             // sunk into it and held all at once
             const float acc = lookup_sum<S::NF, S::FB>(reinterpret_cast<const char *>(tab), 0u, k.w[u]);
@@ -329,8 +334,8 @@ __global__ __launch_bounds__(256) void score_kernel(const SArgs a)
                 val = fmaf(k.gam[u], acc2, val);
             }
             asm volatile("" ::"v"(val));
-            if (k.ok[u])
-                *dst = val;
+            if (k.ok[u] || k.t[u] < tfill)
+                out[k.t[u]] = k.ok[u] ? val : -INFINITY;
         }
     };
     // 3. sums, batch by batch (the next batch's loads issued first)
@@ -342,6 +347,9 @@ __global__ __launch_bounds__(256) void score_kernel(const SArgs a)
             issue(b + 1, kb[(b + 1) & 1]);
         consume(kb[b & 1]);
     }
+    constexpr int kBatch = 256 * S::KPT;
+    for (int64_t t = t0 + (tend - t0 + kBatch - 1) / kBatch * kBatch + threadIdx.x; t < tfill; t += 256)
+        out[t] = -INFINITY;
 }
 
 }  // namespace

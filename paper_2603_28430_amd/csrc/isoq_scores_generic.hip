@@ -35,8 +35,14 @@ __global__ __launch_bounds__(256) void generic_score_kernel(const SArgs a, const
     len = min(len, a.max_len);
     len = min(len, (int64_t)a.max_blocks * a.block_size);
     const int64_t t0 = (int64_t)blockIdx.y * kScoreChunk;
-    if (t0 >= len)
-        return;  // block-uniform: the whole workgroup leaves before the barrier
+    // positions below tfill without a key get -inf (none unless asked for)
+    const int64_t tfill = a.fill ? min(t0 + (int64_t)kScoreChunk, a.max_len) : 0;
+    float *dst = a.scores + ((int64_t)s * a.n_q_heads + hq) * a.max_len;
+    if (t0 >= len) {  // block-uniform: the whole workgroup leaves before the barrier
+        for (int64_t t = t0 + threadIdx.x; t < tfill; t += blockDim.x)
+            dst[t] = -INFINITY;
+        return;
+    }
     const int set = a.n_sets == 1 ? 0 : h;
 
     if (threadIdx.x < K)
@@ -65,12 +71,16 @@ __global__ __launch_bounds__(256) void generic_score_kernel(const SArgs a, const
 
     const int64_t tend = min(t0 + (int64_t)kScoreChunk, len);
     const int32_t *table = a.block_table + (int64_t)s * a.max_blocks;
-    float *dst = a.scores + ((int64_t)s * a.n_q_heads + hq) * a.max_len;
+    for (int64_t t = tend + threadIdx.x; t < tfill; t += blockDim.x)
+        dst[t] = -INFINITY;
     for (int64_t t = t0 + threadIdx.x; t < tend; t += blockDim.x) {
         const uint32_t bi = fast_div((uint32_t)t, a.div_block);
         const int32_t blk = table[bi];
-        if (blk < 0 || blk >= a.n_blocks)
+        if (blk < 0 || blk >= a.n_blocks) {
+            if (t < tfill)
+                dst[t] = -INFINITY;
             continue;
+        }
         const int pos = (int)((uint32_t)t - bi * a.block_size);
         const int64_t krow = ((int64_t)blk * a.n_kv_heads + h) * a.block_size + pos;
         // the record, piece-major in its head's block region

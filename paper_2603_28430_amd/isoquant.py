@@ -60,6 +60,7 @@ def _load():
     L.isoq_kv_append_qjl.argtypes = [vp, vp, c_int, vp, vp, i64, c_int, vp, vp, vp, vp, i64, c_int, vp]
     L.isoq_kv_scores_qjl.argtypes = [vp, vp, c_int, vp, c_int, c_int, c_int, vp, vp, vp, vp, i64, c_int, vp, c_int,
                                      vp, ctypes.c_float, vp, i64, vp]
+    L.isoq_kv_scores_filled.argtypes = L.isoq_kv_scores_qjl.argtypes
     L.isoq_kv_scores.argtypes = [vp, c_int, vp, c_int, c_int, c_int, vp, vp, i64, c_int, vp, c_int, vp,
                                  ctypes.c_float, vp, i64, vp]
     L.isoq_packed_bytes.argtypes = [c_int, c_int]
@@ -78,8 +79,8 @@ def _load():
     L.isoq_last_hip_error.restype = ctypes.c_char_p
     for f in ("isoq_params_init", "isoq_params_destroy", "isoq_params_export", "isoq_params_info",
               "isoq_quantize", "isoq_dequantize", "isoq_roundtrip", "isoq_kv_append", "isoq_kv_scores", "isoq_sketch_init",
-              "isoq_sketch_destroy", "isoq_sketch_export", "isoq_quantize_qjl", "isoq_kv_scores_qjl",
-              "isoq_codebook_lloyd",
+              "isoq_sketch_destroy", "isoq_sketch_export", "isoq_quantize_qjl", "isoq_kv_append_qjl",
+              "isoq_kv_scores_qjl", "isoq_kv_scores_filled", "isoq_codebook_lloyd",
               "isoq_rotation_draws"):
         getattr(L, f).restype = c_int
     return L
@@ -140,6 +141,7 @@ class Params:
     def __init__(self, handle: int, variant: int, d: int, bits: int, n_sets: int):
         self.handle = ctypes.c_void_p(handle)
         self.variant, self.d, self.bits, self.n_sets = variant, d, bits, n_sets
+        self.record_bytes = isoq_record_bytes(variant, d, bits)
 
     def close(self):
         if self.handle:
@@ -151,10 +153,6 @@ class Params:
             self.close()
         except Exception:
             pass
-
-    @property
-    def record_bytes(self) -> int:
-        return isoq_record_bytes(self.variant, self.d, self.bits)
 
 
 def isoq_params_init(variant, d: int, bits: int, n_sets: int = 1, rot=None, codebook=None,
@@ -198,15 +196,27 @@ def isoq_params_info(p: Params):
 
 
 # --- device calls ----------------------------------------------------------------
+# A decode step's kernels run for about 5 us, so the calls below are written for
+# few Python operations: pointers and sizes go to ctypes as plain integers (its
+# argument types are declared above), shapes are compared as the tuples that
+# they are, and a failed placement test is spelled out only after it failed.
+try:
+    import torch as _torch_module
+except ImportError:
+    _torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    if _torch_module is None:
+        raise ImportError("the device calls need torch")
+    return _torch_module
 
 
-def _stream_ptr(stream):
-    torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+def _stream_ptr(stream) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    c = _torch()._C
+    return c._cuda_getCurrentRawStream(c._cuda_getDevice())   # of torch.cuda.current_stream()
 
 
 def _dtype_code(t) -> int:
@@ -252,6 +262,14 @@ def _device_tensors(ref, **ts):
             raise ValueError(f"{name} must be on {ref.device}, got {t.device}")
 
 
+def _placed(ref, ts):
+    """_device_tensors for the decoding calls, the tensors named by their place."""
+    dev = ref.get_device()
+    for t in ts:
+        if not (_is_gpu(t) and t.is_contiguous() and t.get_device() == dev):
+            _device_tensors(ref, **{f"arg{i}": t for i, t in enumerate(ts)})
+
+
 def isoq_roundtrip(p: Params, x, rows_per_set: int = 1, x_hat=None, stream=None):
     """x_hat = stage-1 quantize->dequantize of x (same shape and dtype)."""
     n = _rows(x, p.d)
@@ -260,8 +278,8 @@ def isoq_roundtrip(p: Params, x, rows_per_set: int = 1, x_hat=None, stream=None)
         x_hat = _torch().empty_like(x)
     _like("x_hat", x_hat, (x.dtype,), n * p.d)
     _device_tensors(x, x_hat=x_hat)
-    _check(lib.isoq_roundtrip(p.handle, _dtype_code(x.dtype), ctypes.c_void_p(x.data_ptr()), n,
-                              int(rows_per_set), ctypes.c_void_p(x_hat.data_ptr()), _stream_ptr(stream)),
+    _check(lib.isoq_roundtrip(p.handle, _dtype_code(x.dtype), x.data_ptr(), n,
+                              int(rows_per_set), x_hat.data_ptr(), _stream_ptr(stream)),
            "isoq_roundtrip")
     return x_hat
 
@@ -278,9 +296,9 @@ def isoq_quantize(p: Params, x, rows_per_set: int = 1, idx_packed=None, norms=No
     _like("idx_packed", idx_packed, (torch.uint8,), n * p.record_bytes)
     _like("norms", norms, (torch.float32,), n)
     _device_tensors(x, idx_packed=idx_packed, norms=norms)
-    _check(lib.isoq_quantize(p.handle, _dtype_code(x.dtype), ctypes.c_void_p(x.data_ptr()), n,
-                             int(rows_per_set), ctypes.c_void_p(idx_packed.data_ptr()),
-                             ctypes.c_void_p(norms.data_ptr()), _stream_ptr(stream)), "isoq_quantize")
+    _check(lib.isoq_quantize(p.handle, _dtype_code(x.dtype), x.data_ptr(), n,
+                             int(rows_per_set), idx_packed.data_ptr(),
+                             norms.data_ptr(), _stream_ptr(stream)), "isoq_quantize")
     return idx_packed, norms
 
 
@@ -298,14 +316,14 @@ def isoq_dequantize(p: Params, idx_packed, norms, dtype=None, rows_per_set: int 
     if dtype is not None and x_hat.dtype != dtype:
         raise TypeError(f"x_hat is {x_hat.dtype}, dtype asks for {dtype}")
     _device_tensors(norms, idx_packed=idx_packed, x_hat=x_hat)
-    _check(lib.isoq_dequantize(p.handle, _dtype_code(x_hat.dtype), ctypes.c_void_p(idx_packed.data_ptr()),
-                               ctypes.c_void_p(norms.data_ptr()), n, int(rows_per_set),
-                               ctypes.c_void_p(x_hat.data_ptr()), _stream_ptr(stream)), "isoq_dequantize")
+    _check(lib.isoq_dequantize(p.handle, _dtype_code(x_hat.dtype), idx_packed.data_ptr(),
+                               norms.data_ptr(), n, int(rows_per_set),
+                               x_hat.data_ptr(), _stream_ptr(stream)), "isoq_dequantize")
     return x_hat
 
 
 def _ptr(t):
-    return ctypes.c_void_p(None if t is None else t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def isoq_kv_append(pk: Params, k_new, slot_mapping, k_idx, k_rho, pv: Params = None, v_new=None,
@@ -318,30 +336,32 @@ def isoq_kv_append(pk: Params, k_new, slot_mapping, k_idx, k_rho, pv: Params = N
     P bytes, P = 16 or 8 when it divides record_bytes, else P = record_bytes:
     piece j of position s at byte (j block_size + s) P)."""
     torch = _torch()
-    if k_new.dim() != 3 or k_idx.dim() != 4 or k_rho.dim() != 3:
+    rows, cache = k_new.shape, k_idx.shape
+    if len(rows) != 3 or len(cache) != 4 or k_rho.dim() != 3:
         raise ValueError("k_new [n_tokens, n_heads, d], k_idx [n_blocks, n_heads, block_size, R], "
                          "k_rho [n_blocks, n_heads, block_size]")
-    n_tokens, n_heads, d = k_new.shape
-    n_blocks, nh, block_size, rb = k_idx.shape
-    if d != pk.d or nh != n_heads or rb != pk.record_bytes or tuple(k_rho.shape) != (n_blocks, nh, block_size):
+    n_tokens, n_heads, d = rows
+    n_blocks, nh, block_size, rb = cache
+    if d != pk.d or nh != n_heads or rb != pk.record_bytes or k_rho.shape != cache[:3]:
         raise ValueError("cache shapes do not match the rows and the handle")
     if slot_mapping.dtype != torch.int64 or slot_mapping.numel() != n_tokens:
         raise ValueError("slot_mapping must be int64 [n_tokens]")
     if k_idx.dtype != torch.uint8 or k_rho.dtype != torch.float32:
         raise TypeError("k_idx uint8, k_rho float32")
-    ts = [k_new, slot_mapping, k_idx, k_rho]
-    if v_new is not None:
+    dtype = k_new.dtype
+    if v_new is None:
+        _placed(k_new, (k_new, slot_mapping, k_idx, k_rho))
+    else:
         if pv is None or v_idx is None or v_rho is None:
             raise ValueError("v_new needs pv, v_idx and v_rho")
-        if (tuple(v_new.shape) != tuple(k_new.shape) or tuple(v_idx.shape) != tuple(k_idx.shape)
-                or tuple(v_rho.shape) != tuple(k_rho.shape) or v_new.dtype != k_new.dtype):
+        if v_new.shape != rows or v_idx.shape != cache or v_rho.shape != cache[:3] or v_new.dtype != dtype:
             raise ValueError("V tensors must have the shapes and dtype of the K tensors")
-        ts += [v_new, v_idx, v_rho]
-    _device_tensors(k_new, **{f"arg{i}": t for i, t in enumerate(ts)})
-    _check(lib.isoq_kv_append(pk.handle, None if pv is None else pv.handle, _dtype_code(k_new.dtype),
-                              _ptr(k_new), _ptr(v_new), _ptr(slot_mapping), int(n_tokens), int(n_heads),
-                              _ptr(k_idx), _ptr(k_rho), _ptr(v_idx), _ptr(v_rho), int(n_blocks),
-                              int(block_size), _stream_ptr(stream)), "isoq_kv_append")
+        _placed(k_new, (k_new, slot_mapping, k_idx, k_rho, v_new, v_idx, v_rho))
+    st = lib.isoq_kv_append(pk.handle, None if pv is None else pv.handle, _dtype_code(dtype), k_new.data_ptr(),
+                            _ptr(v_new), slot_mapping.data_ptr(), n_tokens, n_heads, k_idx.data_ptr(),
+                            k_rho.data_ptr(), _ptr(v_idx), _ptr(v_rho), n_blocks, block_size, _stream_ptr(stream))
+    if st:
+        _check(st, "isoq_kv_append")
 
 
 def isoq_kv_scores(pk: Params, q, k_idx, k_rho, block_table, seq_lens, scale: float = 1.0,
@@ -359,44 +379,57 @@ def isoq_kv_scores(pk: Params, q, k_idx, k_rho, block_table, seq_lens, scale: fl
         raise ValueError("q [n_seqs, n_q_heads, d], k_idx [n_blocks, n_kv_heads, block_size, R], "
                          "k_rho [n_blocks, n_kv_heads, block_size], block_table [n_seqs, max_blocks]")
     n_seqs, n_q_heads, d = q.shape
-    n_blocks, n_kv_heads, block_size, rb = k_idx.shape
-    if d != pk.d or rb != pk.record_bytes or tuple(k_rho.shape) != (n_blocks, n_kv_heads, block_size):
+    cache = k_idx.shape
+    n_blocks, n_kv_heads, block_size, rb = cache
+    if d != pk.d or rb != pk.record_bytes or k_rho.shape != cache[:3]:
         raise ValueError("cache shapes do not match the queries and the handle")
-    if block_table.shape[0] != n_seqs or seq_lens.numel() != n_seqs:
+    rows, max_blocks = block_table.shape
+    if rows != n_seqs or seq_lens.numel() != n_seqs:
         raise ValueError("block_table and seq_lens need one row per sequence")
     if block_table.dtype != torch.int32 or seq_lens.dtype != torch.int32:
         raise TypeError("block_table and seq_lens must be int32")
-    max_blocks = block_table.shape[1]
     if max_len is None:
         max_len = max_blocks * block_size
-    if scores is None:
-        # positions the kernel does not write (at or past a sequence's
-        # length, or behind an invalid block-table entry) read as -inf, so a
-        # softmax over max_len ignores them
-        scores = torch.full((n_seqs, n_q_heads, max_len), float("-inf"), dtype=torch.float32, device=q.device)
-    elif tuple(scores.shape) != (n_seqs, n_q_heads, max_len) or scores.dtype != torch.float32:
+    shape = (n_seqs, n_q_heads, max_len)
+    # positions without a key (at or past a sequence's length, or behind an
+    # invalid block-table entry) read as -inf in a tensor allocated here, so a
+    # softmax over max_len ignores them: written by the same launch (which
+    # takes max_len up to _FILL_MAX) instead of a pass of their own
+    filled = scores is None and 0 < max_len <= _FILL_MAX
+    if filled:
+        scores = torch.empty(shape, dtype=torch.float32, device=q.device)
+    elif scores is None:
+        scores = torch.full(shape, float("-inf"), dtype=torch.float32, device=q.device)
+    elif scores.shape != shape or scores.dtype != torch.float32:
         raise ValueError("scores must be fp32 [n_seqs, n_q_heads, max_len]")
-    ts = [q, k_idx, k_rho, block_table, seq_lens, scores]
-    if sketch is not None:
+    if sketch is None:
+        k_signs = k_gamma = None
+        _placed(q, (q, k_idx, k_rho, block_table, seq_lens, scores))
+    else:
         if k_signs is None or k_gamma is None:
             raise ValueError("a sketch needs k_signs and k_gamma")
-        if (tuple(k_signs.shape) != (n_blocks, n_kv_heads, block_size, sketch.m // 8) or k_signs.dtype != torch.uint8
-                or tuple(k_gamma.shape) != tuple(k_rho.shape) or k_gamma.dtype != torch.float32):
+        if (k_signs.shape != cache[:3] + (sketch.m // 8,) or k_signs.dtype != torch.uint8
+                or k_gamma.shape != cache[:3] or k_gamma.dtype != torch.float32):
             raise ValueError("k_signs [n_blocks, n_kv_heads, block_size, m/8] uint8, k_gamma like k_rho")
-        ts += [k_signs, k_gamma]
-    _device_tensors(q, **{f"arg{i}": t for i, t in enumerate(ts)})
-    if sketch is None:
-        _check(lib.isoq_kv_scores(pk.handle, _dtype_code(q.dtype), _ptr(q), int(n_seqs), int(n_q_heads),
-                                  int(n_kv_heads), _ptr(k_idx), _ptr(k_rho), int(n_blocks), int(block_size),
-                                  _ptr(block_table), int(max_blocks), _ptr(seq_lens), float(scale),
-                                  _ptr(scores), int(max_len), _stream_ptr(stream)), "isoq_kv_scores")
+        _placed(q, (q, k_idx, k_rho, block_table, seq_lens, scores, k_signs, k_gamma))
+    cache_args = (n_blocks, block_size, block_table.data_ptr(), max_blocks, seq_lens.data_ptr(), float(scale),
+                  scores.data_ptr(), max_len, _stream_ptr(stream))
+    head_args = (_dtype_code(q.dtype), q.data_ptr(), n_seqs, n_q_heads, n_kv_heads, k_idx.data_ptr(),
+                 k_rho.data_ptr())
+    if filled:
+        st = lib.isoq_kv_scores_filled(pk.handle, None if sketch is None else sketch.handle, *head_args,
+                                       _ptr(k_signs), _ptr(k_gamma), *cache_args)
+    elif sketch is None:
+        st = lib.isoq_kv_scores(pk.handle, *head_args, *cache_args)
     else:
-        _check(lib.isoq_kv_scores_qjl(pk.handle, sketch.handle, _dtype_code(q.dtype), _ptr(q), int(n_seqs),
-                                      int(n_q_heads), int(n_kv_heads), _ptr(k_idx), _ptr(k_rho), _ptr(k_signs),
-                                      _ptr(k_gamma), int(n_blocks), int(block_size), _ptr(block_table),
-                                      int(max_blocks), _ptr(seq_lens), float(scale), _ptr(scores), int(max_len),
-                                      _stream_ptr(stream)), "isoq_kv_scores_qjl")
+        st = lib.isoq_kv_scores_qjl(pk.handle, sketch.handle, *head_args, k_signs.data_ptr(), k_gamma.data_ptr(),
+                                    *cache_args)
+    if st:
+        _check(st, "isoq_kv_scores" if sketch is None else "isoq_kv_scores_qjl")
     return scores
+
+
+_FILL_MAX = 65535 * 1024   # the filled call's largest max_len
 
 
 def isoq_kv_scores_qjl(pk: Params, sketch, q, k_idx, k_rho, k_signs, k_gamma, block_table, seq_lens,
@@ -492,17 +525,17 @@ def isoq_kv_append_qjl(pk: Params, sk: Sketch, k_new, slot_mapping, k_idx, k_rho
     n_tokens, n_heads, d = k_new.shape
     n_blocks, nh, block_size, rb = k_idx.shape
     cache = (n_blocks, nh, block_size)
-    if (d != pk.d or nh != n_heads or rb != pk.record_bytes or tuple(k_rho.shape) != cache
-            or tuple(k_gamma.shape) != cache or tuple(k_signs.shape) != cache + (sk.m // 8,)):
+    if (d != pk.d or nh != n_heads or rb != pk.record_bytes or k_rho.shape != cache
+            or k_gamma.shape != cache or k_signs.shape != cache + (sk.m // 8,)):
         raise ValueError("cache shapes do not match the rows, the handle and the sketch")
     if slot_mapping.dtype != torch.int64 or slot_mapping.numel() != n_tokens:
         raise ValueError("slot_mapping must be int64 [n_tokens]")
     if (k_idx.dtype != torch.uint8 or k_signs.dtype != torch.uint8 or k_rho.dtype != torch.float32
             or k_gamma.dtype != torch.float32):
         raise TypeError("k_idx and k_signs uint8, k_rho and k_gamma float32")
-    _device_tensors(k_new, k_new=k_new, slot_mapping=slot_mapping, k_idx=k_idx, k_rho=k_rho, k_signs=k_signs,
-                    k_gamma=k_gamma)
-    _check(lib.isoq_kv_append_qjl(pk.handle, sk.handle, _dtype_code(k_new.dtype), _ptr(k_new), _ptr(slot_mapping),
-                                  int(n_tokens), int(n_heads), _ptr(k_idx), _ptr(k_rho), _ptr(k_signs),
-                                  _ptr(k_gamma), int(n_blocks), int(block_size), _stream_ptr(stream)),
-           "isoq_kv_append_qjl")
+    _placed(k_new, (k_new, slot_mapping, k_idx, k_rho, k_signs, k_gamma))
+    st = lib.isoq_kv_append_qjl(pk.handle, sk.handle, _dtype_code(k_new.dtype), k_new.data_ptr(),
+                                slot_mapping.data_ptr(), n_tokens, n_heads, k_idx.data_ptr(), k_rho.data_ptr(),
+                                k_signs.data_ptr(), k_gamma.data_ptr(), n_blocks, block_size, _stream_ptr(stream))
+    if st:
+        _check(st, "isoq_kv_append_qjl")
