@@ -146,18 +146,25 @@ struct CacheSrcRt {
 };
 
 // Index bits of slot j (4 coordinates, BITS each) from a record of nb bytes.
+// These kernels are bound by VALU issue and by the number of accesses, so a
+// slot is one 2-byte access where it can be and lanes take one path: fp16 rows
+// of d = 90, 372,827 of them, dequantize at 3 / 4 bits 31.7 / 27.5 -> 27.5 /
+// 20.1 us (d = 100, 335,544 rows: 29.5 / 23.4 -> 22.9 / 17.5), quantize at 4
+// bits 36.2 -> 32.2 us (with the binary search of gen_ballot_encode4).
 template <int BITS, class Src>
 __device__ __forceinline__ uint32_t gen_read_slot(const Src &rec, int j, int nb)
 {
     auto byte = [&](int k) -> uint32_t { return k < nb ? (uint32_t)rec.template get<uint8_t>(k) : 0u; };
-    if constexpr (BITS == 2)
+    if constexpr (BITS == 2) {
         return byte(j);
-    else if constexpr (BITS == 4)
-        return byte(2 * j) | (byte(2 * j + 1) << 8);
-    else if ((j & 1) == 0)   // bits 12 j .. 12 j + 11 start on a byte boundary
-        return byte(3 * j / 2) | ((byte(3 * j / 2 + 1) & 0xFu) << 8);
-    else                     // ... or in the middle of byte (3 j - 1) / 2
-        return (byte((3 * j - 1) / 2) >> 4) | (byte((3 * j + 1) / 2) << 4);
+    } else if constexpr (BITS == 4) {   // a slot's two bytes together where records are a whole number of half-words
+        return nb % 2 == 0 ? (uint32_t)rec.template get<uint16_t>(2 * j) : byte(2 * j) | (byte(2 * j + 1) << 8);
+    } else {
+        // bits 12 j .. 12 j + 11: from byte 3 j / 2 on, an odd slot's in the
+        // middle of it (one form for both, so that lanes do not diverge)
+        const int k = (3 * j) >> 1;
+        return ((byte(k) | (byte(k + 1) << 8)) >> (4 * (j & 1))) & 0xFFFu;
+    }
 }
 
 // Write the bytes whose first bit lies in slot j's bit range; `next` is the
@@ -173,8 +180,12 @@ __device__ __forceinline__ void gen_write_slot(const Dst &rec, int j, int nb, ui
     if constexpr (BITS == 2) {
         put(j, p);
     } else if constexpr (BITS == 4) {
-        put(2 * j, p);
-        put(2 * j + 1, p >> 8);
+        if (nb % 2 == 0) {
+            rec.template put<uint16_t>(2 * j, (uint16_t)p);
+        } else {
+            put(2 * j, p);
+            put(2 * j + 1, p >> 8);
+        }
     } else if ((j & 1) == 0) {
         put(3 * j / 2, p);
         put(3 * j / 2 + 1, (p >> 8) | ((next & 0xFu) << 4));
@@ -211,17 +222,17 @@ __device__ __forceinline__ void gen_write_slot8(const Dst &rec, int j, uint32_t 
     }
 }
 
-// 2 and 3 bits, encoders: the index bits of a slot's 4 coordinates from lane
-// masks, as the tuned kernels' ballot_encode does for 8: the top bit of a
-// coordinate's index is its sign decision (y > 0) and each lower bit the
-// matching bit of the magnitude index (3 bits: a compare with the middle
-// positive threshold, then with the one it selects), inverted when y <= 0;
-// the masks are pushed into the word from its top, coordinate 3 first.
-// Every lane of the wave must call it.
+// Encoders: the index bits of a slot's 4 coordinates from lane masks, as the
+// tuned kernels' ballot_encode does for 8: the top bit of a coordinate's index
+// is its sign decision (y > 0) and each lower bit the matching bit of the
+// magnitude index (binary search: a compare with the middle positive
+// threshold, then with the ones it selects), inverted when y <= 0; the masks
+// are pushed into the word from its top, coordinate 3 first.  At 4 bits that
+// is 12 instructions per coordinate; counting the 7 thresholds took 18.  Every
+// lane of the wave must call it.
 template <int BITS>
 __device__ __forceinline__ uint32_t gen_ballot_encode4(const float y[4], const float *ths)
 {
-    static_assert(BITS == 2 || BITS == 3, "2 or 3 bits");
     uint64_t mk[4 * BITS];
 #pragma unroll
     for (int c = 0; c < 4; c++) {
@@ -230,7 +241,15 @@ __device__ __forceinline__ uint32_t gen_ballot_encode4(const float y[4], const f
         uint64_t *o = mk + c * BITS;
         const uint64_t pos = __builtin_amdgcn_ballot_w64(y[j] > 0.f);
         o[0] = pos;
-        if constexpr (BITS == 3) {
+        if constexpr (BITS == 4) {
+            const bool b2 = m > ths[3];
+            const bool b1 = m > (b2 ? ths[5] : ths[1]);
+            const float upper = b1 ? ths[6] : ths[4], lower = b1 ? ths[2] : ths[0];
+            const bool b0 = m > (b2 ? upper : lower);
+            o[1] = ~(__builtin_amdgcn_ballot_w64(b2) ^ pos);
+            o[2] = ~(__builtin_amdgcn_ballot_w64(b1) ^ pos);
+            o[3] = ~(__builtin_amdgcn_ballot_w64(b0) ^ pos);
+        } else if constexpr (BITS == 3) {
             const bool hi = m > ths[1];
             const bool lo = m > (hi ? ths[2] : ths[0]);
             o[1] = ~(__builtin_amdgcn_ballot_w64(hi) ^ pos);
@@ -239,7 +258,9 @@ __device__ __forceinline__ uint32_t gen_ballot_encode4(const float y[4], const f
             o[1] = ~(__builtin_amdgcn_ballot_w64(m > ths[0]) ^ pos);
         }
     }
-    if constexpr (BITS == 3)
+    if constexpr (BITS == 4)
+        return push_bits8(push_bits8(0u, mk), mk + 8);
+    else if constexpr (BITS == 3)
         return push_bits12(0u, mk);
     else
         return push_bits8(0u, mk);
@@ -369,7 +390,7 @@ __global__ __launch_bounds__(kBlockThreads) void generic_kernel(const KArgs a)
                 else
                     rotate4_forward<VAR>(P[k], xv[k], y);
                 uint32_t p = 0;
-                if constexpr (kEncode && SW == 4 && BITS <= 3) {
+                if constexpr (kEncode && SW == 4) {
                     p = gen_ballot_encode4<BITS>(y, ths);
                 } else {
 #pragma unroll
