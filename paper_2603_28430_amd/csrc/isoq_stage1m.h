@@ -510,9 +510,7 @@ struct Stage1M {
 #pragma unroll
         for (int j = 0; j < 8; j++)
             m[j] = fabsf(y[j]);
-        // with the sketch the levels are the normalised ones, and zero for a
-        // zero row (whose y is exactly zero), so that e below is zero there
-        const float lscale = kQjl ? (rho > 0.f ? 1.f : 0.f) : rho;
+        const float lscale = kQjl ? 1.f : rho;   // with the sketch the levels are the normalised ones
         uint32_t p = 0;
         if constexpr (kUseLut) {
             const float s = a.lut_inv_h * __builtin_amdgcn_rcpf(rho_e);
@@ -528,17 +526,6 @@ struct Stage1M {
                 for (int k = 0; k < H; k++)
                     lvs[k] = lev[k] * lscale;
                 chain_levels<H>(y, m, ths, lvs, yq);
-            } else if constexpr (kQjl) {
-                float lvs[H];
-#pragma unroll
-                for (int k = 0; k < H; k++)
-                    lvs[k] = lev[k];
-                if (__builtin_amdgcn_ballot_w64(rho == 0.f) != 0) {   // rare, and the same for the whole wave
-#pragma unroll
-                    for (int k = 0; k < H; k++)
-                        lvs[k] *= lscale;
-                }
-                p = ballot_encode<BITS, kQjl>(y, m, ths, lvs, yq);
             } else {
                 p = ballot_encode<BITS, kQjl>(y, m, ths, lev, yq);
             }
@@ -597,7 +584,19 @@ struct Stage1M {
         if constexpr (kQjl) {
             // e = y / rho' - c[idx], the normalised rotated-domain error (zero
             // for a zero row); -e to the block's LDS tile as fp16
-            const float inv = __builtin_amdgcn_rcpf(rho_e);
+            float inv = __builtin_amdgcn_rcpf(rho_e);
+            // (and for a row with an infinity or NaN, where a result's sign
+            // would say nothing: every sign 0 and gamma NaN); rare, and the
+            // branch is the same for the whole wave
+            const bool odd_row = __builtin_amdgcn_classf(rho, 0x267);   // zero, infinite or NaN
+            if (__builtin_amdgcn_ballot_w64(odd_row) != 0) {
+                inv = odd_row ? 0.f : inv;
+#pragma unroll
+                for (int j = 0; j < 8; j++) {
+                    y[j] = odd_row ? 0.f : y[j];
+                    yq[j] = odd_row ? 0.f : yq[j];
+                }
+            }
             float e[8];
 #pragma unroll
             for (int j = 0; j < 8; j++) {

@@ -394,8 +394,9 @@ def isoq_kv_scores(pk: Params, q, k_idx, k_rho, block_table, seq_lens, scale: fl
     # positions without a key (at or past a sequence's length, or behind an
     # invalid block-table entry) read as -inf in a tensor allocated here, so a
     # softmax over max_len ignores them: written by the same launch (which
-    # takes max_len up to _FILL_MAX) instead of a pass of their own
-    filled = scores is None and 0 < max_len <= _FILL_MAX
+    # takes max_len up to _FILL_MAX) instead of a pass of their own, unless there
+    # is no key at all
+    filled = scores is None and 0 < max_len <= _FILL_MAX and n_blocks > 0 and max_blocks > 0
     if filled:
         scores = torch.empty(shape, dtype=torch.float32, device=q.device)
     elif scores is None:
@@ -413,7 +414,7 @@ def isoq_kv_scores(pk: Params, q, k_idx, k_rho, block_table, seq_lens, scale: fl
             raise ValueError("k_signs [n_blocks, n_kv_heads, block_size, m/8] uint8, k_gamma like k_rho")
         _placed(q, (q, k_idx, k_rho, block_table, seq_lens, scores, k_signs, k_gamma))
     cache_args = (n_blocks, block_size, block_table.data_ptr(), max_blocks, seq_lens.data_ptr(), float(scale),
-                  scores.data_ptr(), max_len, _stream_ptr(stream))
+                  scores.data_ptr(), int(max_len), _stream_ptr(stream))
     head_args = (_dtype_code(q.dtype), q.data_ptr(), n_seqs, n_q_heads, n_kv_heads, k_idx.data_ptr(),
                  k_rho.data_ptr())
     if filled:
