@@ -334,8 +334,12 @@ __global__ __launch_bounds__(256) void score_kernel(const SArgs a)
                 val = fmaf(k.gam[u], acc2, val);
             }
             asm volatile("" ::"v"(val));
-            if (k.ok[u] || k.t[u] < tfill)
-                out[k.t[u]] = k.ok[u] ? val : -INFINITY;
+            // two branches and no select: waves whose keys are all there (almost
+            // all) spend no vector instruction on the filling
+            if (k.ok[u])
+                out[k.t[u]] = val;
+            else if (k.t[u] < tfill)
+                out[k.t[u]] = -INFINITY;
         }
     };
     // 3. sums, batch by batch (the next batch's loads issued first)
