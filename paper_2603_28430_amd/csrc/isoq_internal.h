@@ -340,7 +340,7 @@ static_assert(sizeof(LutEntry) == 16, "LUT entries are 16 bytes");
 bool build_magnitude_lut(int H, const double *tau, const double *lev, double *inv_h,
                          std::vector<LutEntry> &lut);
 // The levels (symmetric, ascending, 2^bits of them) as digits, one set or,
-// where that leaves a level off by more than 2^-20 of itself, further sets for
+// where that leaves a level off by more than 2^-23 of itself, further sets for
 // the remainders.
 void build_level_digits(int bits, const float *levels, std::vector<LevelDigits> &out);
 // Lloyd-Max levels for N(0, sigma^2) (ascending, symmetrised).

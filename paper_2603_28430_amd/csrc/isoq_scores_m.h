@@ -18,7 +18,7 @@
 // (4 bits: c_k = quantum (int + (1 + 256 + 256^2) / 2), so that a level's
 // mirror image is the complement of its digits).  The quantum is searched so
 // that the integers hit the levels (build_level_digits); a codebook that one
-// set of digits does not hold to 2^-20 of each level takes further passes over
+// set of digits does not hold to 2^-23 of each level takes further passes over
 // the residual levels.  Against 64 bits the logits are off by 5e-8 of their
 // rms; the fp32 lookup tables that this replaces were off by 1.3e-7.
 //

@@ -8,8 +8,8 @@ non-finite queries.
 
 Tolerances are those of test_gpu_kv_scores.py and test_gpu_kv_scores_qjl.py
 (the bound of an fp32 sum of lookups).  The digits stay inside it: a level is
-off by at most 2^-20 of itself and 2^-24 of the largest level on average, the
-query by 2^-31 of its largest coordinate, and the int32 sums are exact.
+off by at most 2^-23 of itself, the query by 2^-31 of its largest coordinate,
+and the int32 sums are exact.
 Needs an MI355X."""
 import numpy as np
 import pytest
@@ -76,6 +76,28 @@ def test_scores_groups_wide_codebook(monkeypatch, bits, ratio):
     plain.run_case("full", 128, bits, "f16", n_seqs=1, n_q=6, n_kv=2, bs=16, seq_lens=[300], seed=bits)
     small = lambda s, h, n: (np.full((n, 128), k, np.uint8), np.ones(n, np.float32))  # noqa: E731
     plain.run_case("full", 128, bits, "f32", n_seqs=1, n_q=6, n_kv=2, bs=16, seq_lens=[70], seed=bits, keys=small)
+
+
+@pytest.mark.parametrize("d", [64, 128, 192, 256])
+@pytest.mark.parametrize("bits", [2, 3, 4])
+def test_scores_groups_small_level_keys(d, bits):
+    """Keys made of the two smallest levels +-c only: their logits are exactly
+    proportional to c, so they are off by what c is off (2^-23 of itself at
+    most) and by the fp32 roundings of the query, of the sum and of its two
+    factors (2^-24 each, 2^-22 together)."""
+    p, rot, levels = plain.make("fast", d, bits, 2)
+    half = 1 << (bits - 1)
+    rng = np.random.default_rng(d + bits)
+    keys = lambda s, h, n: (rng.integers(half - 1, half + 1, (n, d)).astype(np.uint8),  # noqa: E731
+                            rng.uniform(0.5, 2.0, n).astype(np.float32))
+    cache = plain.Cache(rng, d, bits, 1, 2, 16, [400], keys=keys)
+    q = rng.standard_normal((1, 4, d)).astype(np.float32)
+    rec, rho, table, lens = cache.device()
+    got = iq.isoq_kv_scores(p, torch.from_numpy(q).cuda(), rec, rho, table, lens, 1.0)[0, :, :400].cpu().numpy()
+    exp = plain.expected("fast", d, bits, rot, np.float32(levels), 2, q, cache, 1.0, 2)
+    ref = np.stack([exp[0, hq][0] for hq in range(4)])
+    err = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    assert err <= 2.0 ** -23 + 2.0 ** -22, err * 2.0 ** 24
 
 
 def test_scores_groups_nonfinite_query():

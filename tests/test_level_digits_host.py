@@ -1,6 +1,6 @@
 """The codebook's digits for the matrix-core logit kernel (build_level_digits):
-the digits, summed as the kernel sums them, stand for every level to 2^-20 of
-itself; one set of them does for the Lloyd-Max codebooks at every width,
+the digits, summed as the kernel sums them, stand for every level to 2^-23 of
+itself (twice the rounding of a float); one set of them does for the Lloyd-Max codebooks at every width,
 further sets for codebooks whose levels span orders of magnitude; and a
 level's mirror image is exactly its negative.  Runs on the CPU."""
 import os
@@ -39,5 +39,5 @@ def test_level_digits(tmp_path):
         n, *vals = line.split()
         vals, ref = np.array(vals, float), np.float32(c).astype(float)
         assert 1 <= int(n) < 8 and (sets is None or int(n) == sets), (b, n)
-        assert np.all(np.abs(vals - ref) <= 2.0 ** -20 * np.abs(ref)), (b, vals / ref - 1)
+        assert np.all(np.abs(vals - ref) <= 2.0 ** -23 * np.abs(ref)), (b, vals / ref - 1)
         assert np.array_equal(vals, -vals[::-1])
