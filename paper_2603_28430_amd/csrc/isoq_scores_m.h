@@ -116,8 +116,7 @@ __device__ __forceinline__ void digits4(int v, int out[4])
 
 // v as an integer below 2^p, given the largest magnitude mx of its head
 // (mx < 2^E: v 2^(p - E)); the head's values times 2^-(p - E) are restored by
-// one ldexp.  A non-finite query gives non-finite logits through
-// head_exponent's caller.
+// one ldexp.
 __device__ __forceinline__ int head_exponent(float mx, int p)
 {
     return mx > 0.f ? p - __builtin_amdgcn_frexp_expf(mx) : 0;
@@ -214,11 +213,15 @@ __device__ __forceinline__ i32x4 digit_mfma(const uint32_t *a, const uint32_t *b
     }
 }
 
+// Whether a magnitude (its bits) is infinite or NaN.
+__device__ __forceinline__ bool nonfinite(uint32_t bits) { return bits >= 0x7F800000u; }
+
 // Rotate the group's queries (scale folded in): qt[g][D], the raw rows to
-// qraw (if wanted) and the largest magnitude of each head to mx.
+// qraw (if wanted), the largest magnitude of each head to mx and a flag to odd
+// where one is infinite or NaN.
 template <int VAR, int D>
 __device__ __forceinline__ void rotate_queries(const SArgs &a, int s, int h, int set, int G, float *qt, float *qraw,
-                                               uint32_t *mx)
+                                               uint32_t *mx, uint32_t *odd)
 {
     constexpr int LPQ = D / kCoordsPerLane, PL = kLanePL<VAR>;   // chunks per query, parameters per chunk
     for (int i = threadIdx.x; i < G * LPQ; i += blockDim.x) {
@@ -260,6 +263,73 @@ __device__ __forceinline__ void rotate_queries(const SArgs &a, int s, int h, int
                 qraw[g * D + 8 * l + k] = x[k];
         }
         atomicMax(mx + 8 * g, m);
+        if (nonfinite(m))
+            *odd = 1u;
+    }
+}
+
+// A value where it is infinite or NaN, zero where it is not.
+__device__ __forceinline__ float nonfinite_part(float v) { return fabsf(v) < INFINITY ? 0.f : v; }
+
+// What the kernel leaves in the first kOddWords words of its LDS for
+// nonfinite_logits.
+enum { kOddFlag, kOddArgs, kOddX = kOddArgs + 2, kOddY, kOddZ, kOddWords = 8 };
+
+// The workgroup's logits of every head whose query (or S q) is infinite or NaN
+// somewhere, which no digit holds: each is infinite or NaN, by IEEE rules from
+// the signs of the key's levels at those coordinates and of its sketch.  Rare
+// and not tuned; it starts over from what the kernel left in LDS, so that the
+// kernel holds no register for it (the scalar ones are all in use), and every
+// wave goes over all of the positions.
+template <int D, int BITS, int QM>
+__device__ __forceinline__ void nonfinite_logits(const uint32_t *smem)
+{
+    using S = ScoreMShape<D, BITS, QM>;
+    typedef const __attribute__((address_space(4))) SArgs KernArgs;
+    auto word = [&](int i) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)smem[i]); };
+    KernArgs &a = *(KernArgs *)((uint64_t)word(kOddArgs + 1) << 32 | word(kOddArgs));
+    constexpr int64_t RB = (int64_t)D * BITS / 8;
+    const int h = (int)xcd_head(word(kOddX), (uint32_t)a.n_kv_heads, a.block_size * RB % 128 != 0);
+    const int s = (int)word(kOddZ), G = a.group, t0 = (int)word(kOddY) * a.chunk;
+    const int len = (int)min((int64_t)a.seq_lens[s], min(a.max_len, (int64_t)a.max_blocks * a.block_size));
+    const float *qt = reinterpret_cast<const float *>(smem + kOddWords), *sqv = qt + 2 * G * D;
+    const uint32_t *mx = smem + kOddWords + G * (D + 4 * S::ROWW + (QM ? D + QM + 4 * S::SROWW : 0)) + 4;
+    const FastDiv by_block = {a.div_block.m, a.div_block.s1, a.div_block.s2};
+    const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+#pragma unroll 1
+    for (int g = 0; g < G; g++) {
+        if (!nonfinite(mx[8 * g]) && !(QM > 0 && nonfinite(mx[8 * (G + g)])))
+            continue;
+        float *out = a.scores + ((int64_t)s * a.n_q_heads + (int64_t)h * G + g) * a.max_len;
+#pragma unroll 1
+        for (int t = t0 + lane; t < min(t0 + a.chunk, len); t += 64) {
+            const uint32_t bi = fast_div((uint32_t)t, by_block);
+            const int32_t blk = a.block_table[(int64_t)s * a.max_blocks + bi];
+            if (blk < 0 || blk >= a.n_blocks)
+                continue;
+            const int pos = (int)((uint32_t)t - bi * a.block_size);
+            const int64_t krow = ((int64_t)blk * a.n_kv_heads + h) * a.block_size + pos;
+            const uint8_t *rec = a.k_idx + (krow - pos) * RB + (int64_t)pos * S::CP;
+            float acc = 0.f;
+#pragma unroll 1
+            for (int c = 0; c < D; c++) {
+                const int bit = c * BITS + BITS - 1, i = bit >> 3;   // an index's top bit: a positive level
+                const uint32_t byte = rec[(int64_t)(i / S::CP) * a.block_size * S::CP + i % S::CP];
+                const float x = nonfinite_part(qt[g * D + c]);
+                acc += (byte >> (bit & 7)) & 1 ? x : -x;
+            }
+            float v = a.k_rho[krow] * acc;
+            if constexpr (QM > 0) {
+                float acc2 = 0.f;
+#pragma unroll 1
+                for (int r = 0; r < QM; r++) {
+                    const float x = nonfinite_part(sqv[g * QM + r]);
+                    acc2 += (a.k_signs[krow * (QM / 8) + (r >> 3)] >> (r & 7)) & 1 ? x : -x;
+                }
+                v = fmaf(a.k_gamma[krow], acc2, v);
+            }
+            out[t] = v;
+        }
     }
 }
 
@@ -292,12 +362,12 @@ __global__ __launch_bounds__(256) void score_m_kernel(const SArgs a)
                 out[(int64_t)g * a.max_len + t] = -INFINITY;
         return;
     }
-    // LDS per head: rotated query | raw query | S q, then digit rows, digit
-    // sums and largest magnitudes
-    float *qt = reinterpret_cast<float *>(smem);
+    // LDS: kOddWords words for nonfinite_logits, then per head rotated query |
+    // raw query | S q, then digit rows, digit sums and largest magnitudes
+    float *qt = reinterpret_cast<float *>(smem + kOddWords);
     float *qraw = qt + G * D;
     float *sqv = qraw + (QM ? G * D : 0);
-    uint32_t *dig = smem + G * (D + (QM ? D + QM : 0));
+    uint32_t *dig = smem + kOddWords + G * (D + (QM ? D + QM : 0));
     uint32_t *sdig = dig + G * 4 * S::ROWW;
     int *sums = reinterpret_cast<int *>(sdig + (QM ? G * 4 * S::SROWW : 0));   // [G][8]: 4 digit sums, largest magnitude
     int *ssums = sums + G * 8;
@@ -409,13 +479,22 @@ __global__ __launch_bounds__(256) void score_m_kernel(const SArgs a)
         if constexpr (QM > 0)
             ssums[i] = 0;
     }
+    if (threadIdx.x == 255) {   // (a wave with less to do)
+        const uint64_t ka = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+        smem[kOddFlag] = 0u;
+        smem[kOddArgs] = (uint32_t)ka;
+        smem[kOddArgs + 1] = (uint32_t)(ka >> 32);
+        smem[kOddX] = blockIdx.x;
+        smem[kOddY] = blockIdx.y;
+        smem[kOddZ] = blockIdx.z;
+    }
     __syncthreads();
     float *const raw_to = QM ? qraw : nullptr;
     switch (a.variant) {
-    case VAR_FULL: rotate_queries<VAR_FULL, D>(a, s, h, set, G, qt, raw_to, mx); break;
-    case VAR_FAST: rotate_queries<VAR_FAST, D>(a, s, h, set, G, qt, raw_to, mx); break;
-    case VAR_PLANAR2D: rotate_queries<VAR_PLANAR2D, D>(a, s, h, set, G, qt, raw_to, mx); break;
-    default: rotate_queries<VAR_BLOCK8, D>(a, s, h, set, G, qt, raw_to, mx); break;
+    case VAR_FULL: rotate_queries<VAR_FULL, D>(a, s, h, set, G, qt, raw_to, mx, smem + kOddFlag); break;
+    case VAR_FAST: rotate_queries<VAR_FAST, D>(a, s, h, set, G, qt, raw_to, mx, smem + kOddFlag); break;
+    case VAR_PLANAR2D: rotate_queries<VAR_PLANAR2D, D>(a, s, h, set, G, qt, raw_to, mx, smem + kOddFlag); break;
+    default: rotate_queries<VAR_BLOCK8, D>(a, s, h, set, G, qt, raw_to, mx, smem + kOddFlag); break;
     }
     __syncthreads();
 
@@ -484,6 +563,8 @@ __global__ __launch_bounds__(256) void score_m_kernel(const SArgs a)
             const int g = i / (4 * S::SQ), cq = i - g * (4 * S::SQ);
             const int c = cq / S::SQ, q = cq - c * S::SQ;
             const int e = head_exponent(__uint_as_float(smx[8 * g]), 29);
+            if (nonfinite(smx[8 * g]))
+                smem[kOddFlag] = 1u;
             uint32_t word[4] = {0u, 0u, 0u, 0u};
             int sum[4] = {0, 0, 0, 0};
 #pragma unroll
@@ -538,8 +619,7 @@ __global__ __launch_bounds__(256) void score_m_kernel(const SArgs a)
         const int gi = gr < G ? gr : 0;
         const float m = __uint_as_float(mx[8 * gi]);
         const int e = head_exponent(m, QP);
-        // (m - m: 0, or NaN for a non-finite query)
-        t.f1 = __builtin_amdgcn_ldexpf(1.f, -(e / 2)) + (m - m);
+        t.f1 = __builtin_amdgcn_ldexpf(1.f, -(e / 2));
         t.f2 = __builtin_amdgcn_ldexpf(1.f, e / 2 - e);
         if constexpr (!MP)
             t.f1 *= a.lv.quantum;
@@ -557,7 +637,7 @@ __global__ __launch_bounds__(256) void score_m_kernel(const SArgs a)
             }
             const float sm = __uint_as_float(smx[8 * gi]);
             const int se = head_exponent(sm, 29);
-            t.s1 = __builtin_amdgcn_ldexpf(1.f, -(se / 2)) + (sm - sm);
+            t.s1 = __builtin_amdgcn_ldexpf(1.f, -(se / 2));
             t.s2 = __builtin_amdgcn_ldexpf(1.f, se / 2 - se);
             t.ssum = *reinterpret_cast<const i32x4 *>(ssums + 8 * gi);
         }
@@ -753,6 +833,11 @@ __global__ __launch_bounds__(256) void score_m_kernel(const SArgs a)
             if constexpr (!LOOP)
                 break;
         }
+    }
+    // 4. heads that no digit holds, again
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)smem[kOddFlag]) != 0, 0)) {
+        __syncthreads();   // the other waves' stores of step 3 to the same positions
+        nonfinite_logits<D, BITS, QM>(smem);
     }
     // positions of the chunk past the last batch (fill only)
     for (int t = t0 + 256 * nb + (int)threadIdx.x; t < tend; t += 256)

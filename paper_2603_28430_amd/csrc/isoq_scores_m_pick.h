@@ -17,7 +17,7 @@ template <int D, int BITS, int QM>
 ScoreKernel score_m_entry(int group, bool passes)
 {
     using S = ScoreMShape<D, BITS, QM>;
-    const size_t lds = sizeof(uint32_t) * (size_t)group * S::head_words();
+    const size_t lds = sizeof(uint32_t) * (kOddWords + (size_t)group * S::head_words());
     if (passes)
         return {reinterpret_cast<const void *>(&score_m_kernel<D, BITS, QM, 4, 1, true, true>), lds};
     if constexpr (D <= 256) {

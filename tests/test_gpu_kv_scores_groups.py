@@ -100,20 +100,45 @@ def test_scores_groups_small_level_keys(d, bits):
     assert err <= 2.0 ** -23 + 2.0 ** -22, err * 2.0 ** 24
 
 
-def test_scores_groups_nonfinite_query():
-    """A query with an infinity or NaN gives NaN logits, the group's other
-    heads theirs."""
+@pytest.mark.parametrize("d,bits,group,m", [(128, 3, 4, 0), (64, 4, 2, 64), (80, 3, 5, 128), (256, 2, 9, 0),
+                                            (96, 4, 3, 64)])
+def test_scores_groups_nonfinite_query(d, bits, group, m):
+    """A query with an infinity or NaN gives the logits that it gives as the
+    only head of its key head (infinite or NaN as IEEE sums are), the group's
+    other heads theirs; with and without the filling of positions that have no
+    key (a block-table entry out of range, past a length)."""
     rng = np.random.default_rng(5)
-    p, rot, levels = plain.make("fast", 128, 3, 2)
-    cache = plain.Cache(rng, 128, 3, 1, 2, 16, [100])
-    q = rng.standard_normal((1, 8, 128)).astype(np.float32)
+    p, rot, levels = plain.make("fast", d, bits, 2)
+    sk = iq.isoq_sketch_init(p, m) if m else None
+    cache = plain.Cache(rng, d, bits, 2, 2, 16, [300, 41])
+    cache.table[0, 3] = -1
     rec, rho, table, lens = cache.device()
-    ref = iq.isoq_kv_scores(p, torch.from_numpy(q).cuda(), rec, rho, table, lens, 1.0)
+    q = rng.standard_normal((2, 2 * group, d)).astype(np.float32)
+    kw = {}
+    if m:
+        kw = dict(sketch=sk, k_gamma=rho * 0.2, k_signs=torch.from_numpy(
+            rng.integers(0, 256, tuple(rho.shape) + (m // 8,), dtype=np.uint8)).cuda())
+
+    def scores(rows, **more):
+        return iq.isoq_kv_scores(p, torch.from_numpy(np.ascontiguousarray(rows)).cuda(), rec, rho, table, lens, 1.0,
+                                 **kw, **more)
+
+    ref = scores(q)
     bad = q.copy()
-    bad[0, 1, 5], bad[0, 6, 127] = np.inf, np.nan
-    got = iq.isoq_kv_scores(p, torch.from_numpy(bad).cuda(), rec, rho, table, lens, 1.0)
-    for g in range(8):
-        if g in (1, 6):
-            assert torch.isnan(got[0, g, :100]).all()
-        else:
-            assert torch.equal(got[0, g], ref[0, g])
+    bad[0, 1, 5], bad[0, 2 * group - 1, d - 1], bad[1, 0, 3] = np.inf, np.nan, -np.inf
+    odd = {(0, 1), (0, 2 * group - 1), (1, 0)}
+    got = scores(bad)
+    plain_out = torch.full_like(got, float("-inf"))
+    scores(bad, scores=plain_out)
+    assert torch.equal(torch.nan_to_num(got, nan=7.5), torch.nan_to_num(plain_out, nan=7.5))
+    infinite = 0
+    for s in range(2):
+        for hq in range(2 * group):
+            if (s, hq) not in odd:
+                assert torch.equal(got[s, hq], ref[s, hq])
+                continue
+            one = bad[:, [hq % group, group + hq % group]]   # the head as the only one of each key head
+            exp = scores(one)[s, hq // group]
+            assert torch.equal(torch.nan_to_num(got[s, hq], nan=7.5), torch.nan_to_num(exp, nan=7.5)), (s, hq)
+            infinite += int(torch.isposinf(exp).sum())
+    assert m or infinite > 0   # (with a sketch, S q is infinite throughout and its +- sums NaN)
