@@ -464,10 +464,14 @@ void build_level_digits(int bits, const float *levels, std::vector<LevelDigits> 
     // complement of n's digits, -n - 2 half, stands for -(n + half) q
     const int H = 1 << (bits - 1);
     const double half = bits == 4 ? 32896.5 : 0.0, top = 8355000.0;
-    double rest[8], per_level[8];
+    // in units of a power of two that brings the largest level to 0.5 .. 1: the
+    // quanta of any codebook are then ordinary floats
+    int exp = 0;
+    (void)std::frexp(levels[2 * H - 1], &exp);
+    double level[8], rest[8], per_level[8];
     for (int k = 0; k < H; k++) {
-        rest[k] = levels[H + k];
-        per_level[k] = levels[H + k] > 0.f ? 1.0 / levels[H + k] : 0.0;
+        rest[k] = level[k] = std::ldexp((double)levels[H + k], -exp);
+        per_level[k] = level[k] > 0 ? 1.0 / level[k] : 0.0;
     }
     out.clear();
     for (;;) {
@@ -511,10 +515,11 @@ void build_level_digits(int bits, const float *levels, std::vector<LevelDigits> 
             std::memcpy(lv.tab[t], bytes[t], 8);
         // (4 bits: the query side holds digits of twice its integers)
         lv.quantum = (float)(q * (bits == 4 ? 32768.0 : 65536.0));
+        lv.exp = exp;
         out.push_back(lv);
         bool done = true;
         for (int k = 0; k < H; k++)
-            done = done && std::fabs(rest[k]) <= std::ldexp(std::fabs((double)levels[H + k]), -23);
+            done = done && std::fabs(rest[k]) <= std::ldexp(level[k], -23);
         if (done || out.size() == 8)
             return;
     }

@@ -114,11 +114,12 @@ struct KArgs {
 // The codebook as 8-bit digits for the matrix-core logit kernel
 // (isoq_scores_m.h): byte k of tab[t] is digit t (most significant first) of
 // level k's integer (4 bits: of the positive level of magnitude k), and
-// quantum the value of digit weight 256^2 in the kernel's sums.
+// quantum times 2^exp the value of digit weight 256^2 in the kernel's sums
+// (exp is the same in every set of a codebook).
 struct LevelDigits {
     uint32_t tab[3][2];
     float quantum;
-    uint32_t pad;
+    int32_t exp;
 };
 
 // Attention logits against a paged cache of quantized keys (isoq_scores_m.h,

@@ -13,7 +13,7 @@
 // Arithmetic.  Both factors are held as fixed-point integers cut into 8-bit
 // digits, and the digits meet in v_mfma_i32_16x16x64_i8, whose int32 sums are
 // exact:
-//   level  c_k   = quantum (256^2 d_0 + 256 d_1 + d_2),   3 balanced digits
+//   level  c_k   = 2^exp quantum (256^2 d_0 + 256 d_1 + d_2),   3 balanced digits
 //   query  T q   = 2^-e (256^3 l_0 + ... + l_3),          4 balanced digits
 // (4 bits: c_k = quantum (int + (1 + 256 + 256^2) / 2), so that a level's
 // mirror image is the complement of its digits).  The quantum is searched so
@@ -599,7 +599,7 @@ __global__ __launch_bounds__(256) void score_m_kernel(const SArgs a)
         uint32_t A[RG][S::NQ];
         uint32_t Z[RG][S::SQ > 0 ? S::SQ : 1];
         i32x4 sum, ssum;                     // constant terms of the lane's result rows
-        float f1, f2;                        // 2^-e (and the quantum) of the digits, in two factors;
+        float f1, f2;                        // 2^-e (with the quantum) of the digits, in two factors;
         float s1, s2;                        // the sketch's
     };
     auto load_head = [&](int g0, Head &t) {
@@ -618,7 +618,7 @@ __global__ __launch_bounds__(256) void score_m_kernel(const SArgs a)
         }
         const int gi = gr < G ? gr : 0;
         const float m = __uint_as_float(mx[8 * gi]);
-        const int e = head_exponent(m, QP);
+        const int e = head_exponent(m, QP) - a.lv.exp;
         t.f1 = __builtin_amdgcn_ldexpf(1.f, -(e / 2));
         t.f2 = __builtin_amdgcn_ldexpf(1.f, e / 2 - e);
         if constexpr (!MP)

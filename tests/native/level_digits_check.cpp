@@ -1,6 +1,7 @@
 // Prints, for each codebook read from stdin (bits, then 2^bits levels), the
 // number of digit sets and the values that the digits stand for, level by
 // level, as the logit kernel sums them.
+#include <cmath>
 #include <cstdio>
 #include <vector>
 
@@ -32,7 +33,7 @@ int main()
                 }
                 v += bits == 4 ? (n + 32896.5) * ((double)s.quantum / 32768.0) : n * ((double)s.quantum / 65536.0);
             }
-            std::printf(" %.17g", v);
+            std::printf(" %.17g", std::ldexp(v, sets[0].exp));
         }
         std::printf("\n");
     }

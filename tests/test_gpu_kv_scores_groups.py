@@ -100,6 +100,27 @@ def test_scores_groups_small_level_keys(d, bits):
     assert err <= 2.0 ** -23 + 2.0 ** -22, err * 2.0 ** 24
 
 
+@pytest.mark.parametrize("ratio", [None, 1e3])
+def test_scores_groups_codebook_scale(ratio):
+    """Codebooks near the ends of the range of floats (one and several sets of
+    digits): the logits of a codebook times a power of two are the logits times
+    that power, bit for bit."""
+    d, bits = 128, 3
+    levels = np.float32(oracle.codebook(bits, d)).astype(np.float64)
+    if ratio:
+        pos = 0.1 * ratio ** (np.arange(4) / 3 - 1.0)
+        levels = np.concatenate([-pos[::-1], pos]).astype(np.float32).astype(np.float64)
+    rng = np.random.default_rng(9)
+    cache = plain.Cache(rng, d, bits, 1, 2, 16, [200])
+    rec, rho, table, lens = cache.device()
+    q = torch.from_numpy(rng.standard_normal((1, 6, d)).astype(np.float16)).cuda()
+    rot = plain.make("full", d, bits, 2)[1]
+    got = [iq.isoq_kv_scores(iq.isoq_params_init("full", d, bits, 2, rot=rot, codebook=levels * 2.0 ** e), q, rec, rho,
+                             table, lens, 1.0)[0, :, :200].double() * 2.0 ** -e for e in (0, -108, 115)]
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+    assert got[0].abs().min() > 0
+
+
 @pytest.mark.parametrize("d,bits,group,m", [(128, 3, 4, 0), (64, 4, 2, 64), (80, 3, 5, 128), (256, 2, 9, 0),
                                             (96, 4, 3, 64)])
 def test_scores_groups_nonfinite_query(d, bits, group, m):

@@ -1,8 +1,9 @@
 """The codebook's digits for the matrix-core logit kernel (build_level_digits):
 the digits, summed as the kernel sums them, stand for every level to 2^-23 of
-itself (twice the rounding of a float); one set of them does for the Lloyd-Max codebooks at every width,
-further sets for codebooks whose levels span orders of magnitude; and a
-level's mirror image is exactly its negative.  Runs on the CPU."""
+itself (twice the rounding of a float); one set of them does for the Lloyd-Max
+codebooks at every width, at both ends of the range of floats too, further sets
+for codebooks whose levels span orders of magnitude; and a level's mirror image
+is exactly its negative.  Runs on the CPU."""
 import os
 import shutil
 import subprocess
@@ -31,6 +32,8 @@ def test_level_digits(tmp_path):
         for ratio in (2.0, 50.0, 1e3, 1e6):
             pos = 0.3 * ratio ** (np.arange(k) / (k - 1) - 1.0)
             books.append((b, np.concatenate([-pos[::-1], pos]), None))
+    # codebooks at the ends of the range of floats
+    books += [(b, c * scale, sets) for b, c, sets in books[:30:5] for scale in (2.0 ** -115, 2.0 ** 120)]
     text = "".join("%d %s\n" % (b, " ".join("%.9g" % np.float32(v) for v in c)) for b, c, _ in books)
     out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True, timeout=60).stdout
     lines = out.strip().splitlines()
