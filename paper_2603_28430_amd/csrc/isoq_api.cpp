@@ -677,7 +677,7 @@ isoq_status kv_scores_generic(const isoq_params *pk, int dtype, const void *q, i
                               const int32_t *seq_lens, float scale, float *scores, int64_t max_len,
                               int64_t max_pos, bool fill, void *stream)
 {
-    const void *fn = generic_score_kernel_for(pk->variant, pk->bits, dtype == ISOQ_F16);
+    const void *fn = generic_score_kernel_for(pk->variant, pk->bits, dtype == ISOQ_F16, fill);
     if (!fn)
         return ISOQ_E_UNSUPPORTED;
     const int sw = pk->variant == VAR_BLOCK8 ? 8 : 4;
@@ -704,7 +704,6 @@ isoq_status kv_scores_generic(const isoq_params *pk, int dtype, const void *q, i
     a.max_blocks = max_blocks_per_seq;
     a.n_sets = pk->n_sets;
     a.scale = scale;
-    a.fill = fill;
     a.div_block = make_fastdiv((uint32_t)block_size);
     for (int k = 0; k < (1 << pk->bits); k++)
         a.lev_all[k] = pk->levels[k];
@@ -722,10 +721,13 @@ isoq_status kv_scores_generic(const isoq_params *pk, int dtype, const void *q, i
 
 constexpr int64_t kScoreMaxLds = 160 * 1024;   // LDS of one workgroup (gfx950)
 
+// Entries of one query head's lookup tables (isoq_scores.h).
+int table_entries(int d, int bits) { return bits == 4 ? d * 16 : d / 2 * (1 << 2 * bits); }
+
 // Query heads per key head past the limit that the logit calls state.
 bool group_limit(int d, int bits, int group, int m)
 {
-    const int64_t tables = bits == 4 ? d * 16 : d / 2 * (1 << 2 * bits);
+    const int64_t tables = table_entries(d, bits);
     const int64_t sketch = m ? m / 4 * 16 + m + d : 0;
     return 4 * (group * (tables + d + sketch) + 16) > kScoreMaxLds;
 }
@@ -783,8 +785,8 @@ isoq_status kv_scores(const isoq_params *pk, const isoq_sketch *sk, int dtype, c
                                  fill, stream);
     const bool tables = score_by_tables(pk->d, pk->bits, group);
     const ScoreKernel kern = !tables ? score_m_kernel_for(pk->d, pk->bits, group, sk ? sk->m : 0, pk->n_pass > 1)
-                             : sk    ? score_qjl_kernel_for(pk->variant, pk->d, pk->bits, dtype == ISOQ_F16, sk->m)
-                                     : score_kernel_for(pk->variant, pk->d, pk->bits, dtype == ISOQ_F16);
+                             : sk    ? score_qjl_kernel_for(pk->variant, pk->d, pk->bits, dtype == ISOQ_F16, sk->m, fill)
+                                     : score_kernel_for(pk->variant, pk->d, pk->bits, dtype == ISOQ_F16, fill);
     if (!kern.fn)
         return ISOQ_E_UNSUPPORTED;
     const void *fn = kern.fn;
@@ -797,7 +799,7 @@ isoq_status kv_scores(const isoq_params *pk, const isoq_sketch *sk, int dtype, c
         if (e != hipSuccess)
             return hip_fail(e, "hipFuncSetAttribute");
     }
-    SArgs a{};
+    SMArgs a{};   // (the table kernels take its SArgs part)
     a.q = q;
     a.k_idx = k_idx;
     a.k_rho = k_rho;
@@ -828,8 +830,15 @@ isoq_status kv_scores(const isoq_params *pk, const isoq_sketch *sk, int dtype, c
     // rest of its preparation: 8 x 8 x 4 heads, 32,768 keys, m = 128: 60 us at
     // 1,024, 50 us at 2,048 and 4,096), but fewer (512 at least for the
     // tables, whose lanes take two keys, else 256) while that leaves fewer
-    // than four workgroups (sketch: two) per compute unit
-    const int least = tables ? 512 : 256, want = sk && !tables ? 512 : 1024;
+    // than four workgroups per compute unit, or two where a workgroup's
+    // preparation weighs as much as its keys: the sketch, and tables of more
+    // than 3,072 entries.  (Tables, 8 heads, 8,192 keys, 1,024 -> 512: 6
+    // sequences, 384 workgroups of 1,024, d = 128, 2 / 3 / 4 bits and 3 with
+    // 128 sketch bits 6.8 / 8.4 / 10.2 / 13.8 -> 5.6 / 7.7 / 8.0 / 14.0 us; 8
+    // sequences 6.9 / 8.8 / 11.0 / 14.6 -> 6.3 / 9.1 / 9.9 / 16.9 us; 12:
+    // 8.9 / 11.8 / 14.0 / 20.2 -> 8.3 / 11.8 / 14.3 / 26.3 us.)
+    const bool heavy = sk || (tables && table_entries(pk->d, pk->bits) > 3072);
+    const int least = tables ? 512 : 256, want = heavy ? 512 : 1024;
     a.chunk = sk && !tables ? 4 * kScoreChunk : kScoreChunk;
     while (a.chunk > least && (int64_t)n_kv_heads * n_seqs * ((max_pos + a.chunk - 1) / a.chunk) < want)
         a.chunk /= 2;
@@ -839,7 +848,7 @@ isoq_status kv_scores(const isoq_params *pk, const isoq_sketch *sk, int dtype, c
         a.k_gamma = k_gamma;
         a.qjl_scale = (float)((double)scale * std::sqrt(M_PI / 2.0) / sk->m);
     }
-    void *args[] = {&a};
+    void *args[] = {static_cast<SArgs *>(&a)};
     const dim3 grid((unsigned)n_kv_heads, (unsigned)((max_pos + a.chunk - 1) / a.chunk), (unsigned)n_seqs);
     e = hipLaunchKernel(fn, grid, dim3(256), args, lds, static_cast<hipStream_t>(stream));
     if (e != hipSuccess)

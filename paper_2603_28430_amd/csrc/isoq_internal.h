@@ -122,7 +122,7 @@ struct LevelDigits {
     int32_t exp;
 };
 
-// Attention logits against a paged cache of quantized keys (isoq_scores_m.h,
+// Attention logits against a paged cache of quantized keys (isoq_scores.h,
 // isoq_scores_generic.hip).
 struct SArgs {
     const void *q;               // [n_seqs][n_q_heads][d] queries
@@ -135,14 +135,9 @@ struct SArgs {
     int64_t max_len, n_blocks;
     int32_t n_q_heads, n_kv_heads, group, block_size, max_blocks, n_sets;
     float scale;
-    int32_t variant, q_f16;
     int32_t chunk;               // positions per workgroup, a multiple of 256
-    int32_t fill;                // write -inf at positions that have no key
     FastDiv div_block;
     float lev_all[16];           // c_0 .. c_{K-1}
-    LevelDigits lv;              // matrix-core kernel: the first pass over the levels' digits,
-    const LevelDigits *lv_more;  // the others (device memory)
-    int32_t n_pass;
     // stage-2 residual correction (kernels with a sketch only)
     const float *qjl_S;          // [m][d] fp32 projection
     const uint8_t *k_signs;      // [n_blocks][n_kv_heads][block_size][m/8]
@@ -150,9 +145,20 @@ struct SArgs {
     float qjl_scale;             // scale * sqrt(pi/2) / m
     int32_t pad1;
 };
+// The matrix-core kernel's arguments.  (A launch pays for what it passes: with
+// these in SArgs, 56 bytes more, a logit call of one head and 200 keys took 5.1
+// us instead of 4.6.)
+struct SMArgs : SArgs {
+    int32_t variant, q_f16;
+    int32_t fill;                // write -inf at positions that have no key
+    int32_t n_pass;
+    LevelDigits lv;              // the first pass over the levels' digits,
+    const LevelDigits *lv_more;  // the others (device memory)
+};
 
-// Keys per workgroup of the score kernels (the matrix-core kernel takes fewer
-// when that would leave compute units idle, SArgs::chunk).
+// Keys per workgroup of the score kernels, as a rule (SArgs::chunk: fewer where
+// that would leave compute units idle, four times as many on the matrix cores
+// with the sketch).
 constexpr int kScoreChunk = 1024;
 
 // Whether the logits of `group` query heads per key head come from lookup
@@ -164,16 +170,16 @@ constexpr int kScoreChunk = 1024;
 // keys).
 constexpr bool score_by_tables(int d, int bits, int group) { return group == 1 && !(d == 512 && bits >= 3); }
 
-// Score kernel for (variant, d, bits, fp16 queries?) with one query head per
-// key head and the dynamic LDS bytes it needs, or {nullptr, 0}.
+// Score kernel for (variant, d, bits, fp16 queries?, -inf where there is no
+// key?) with one query head per key head and the dynamic LDS bytes it needs, or {nullptr, 0}.
 struct ScoreKernel {
     const void *fn;
     size_t dyn_lds;
 };
-ScoreKernel score_kernel_for(int variant, int d, int bits, bool f16);
-ScoreKernel score_kernel_for_block8(int d, int bits, bool f16);
+ScoreKernel score_kernel_for(int variant, int d, int bits, bool f16, bool fill);
+ScoreKernel score_kernel_for_block8(int d, int bits, bool f16, bool fill);
 // The same with the stage-2 residual correction of m sign bits (isoq_scores_qjl.hip).
-ScoreKernel score_qjl_kernel_for(int variant, int d, int bits, bool f16, int m);
+ScoreKernel score_qjl_kernel_for(int variant, int d, int bits, bool f16, int m, bool fill);
 
 // The matrix-core logit kernel (isoq_scores_m.h, any variant and query type)
 // for width d, bits, query heads per key head and m sketch bits (0: none) and

@@ -108,7 +108,9 @@ __device__ __forceinline__ float lookup_sum(const char *lds, uint32_t base, cons
     return acc[0] + acc[1];
 }
 
-template <int VAR, int D, int BITS, bool F16, int QM>
+// FILL: positions without a key get -inf.  (A kernel of its own: as a run-time
+// switch it cost 0.5 to 1% of the calls that do not ask for it.)
+template <int VAR, int D, int BITS, bool F16, int QM, bool FILL>
 __global__ __launch_bounds__(256) void score_kernel(const SArgs a)
 {
     using S = ScoreShape<D, BITS, QM>;
@@ -125,12 +127,12 @@ __global__ __launch_bounds__(256) void score_kernel(const SArgs a)
     len = min(len, a.max_len);
     len = min(len, (int64_t)a.max_blocks * a.block_size);
     const int64_t t0 = (int64_t)blockIdx.y * a.chunk;
-    // positions below tfill without a key get -inf (none unless asked for)
-    const int64_t tfill = a.fill ? min(t0 + (int64_t)a.chunk, a.max_len) : 0;
+    const int64_t tfill = min(t0 + (int64_t)a.chunk, a.max_len);   // (FILL) end of the chunk
     float *const out = a.scores + ((int64_t)s * a.n_q_heads + h) * a.max_len;
     if (t0 >= len) {  // block-uniform: the whole workgroup leaves before any barrier
-        for (int64_t t = t0 + threadIdx.x; t < tfill; t += 256)
-            out[t] = -INFINITY;
+        if constexpr (FILL)
+            for (int64_t t = t0 + threadIdx.x; t < tfill; t += 256)
+                out[t] = -INFINITY;
         return;
     }
     float *tab = smem;
@@ -334,11 +336,9 @@ __global__ __launch_bounds__(256) void score_kernel(const SArgs a)
                 val = fmaf(k.gam[u], acc2, val);
             }
             asm volatile("" ::"v"(val));
-            // two branches and no select: waves whose keys are all there (almost
-            // all) spend no vector instruction on the filling
             if (k.ok[u])
                 out[k.t[u]] = val;
-            else if (k.t[u] < tfill)
+            else if (FILL && k.t[u] < tfill)
                 out[k.t[u]] = -INFINITY;
         }
     };
@@ -352,8 +352,9 @@ __global__ __launch_bounds__(256) void score_kernel(const SArgs a)
         consume(kb[b & 1]);
     }
     constexpr int kBatch = 256 * S::KPT;
-    for (int64_t t = t0 + (tend - t0 + kBatch - 1) / kBatch * kBatch + threadIdx.x; t < tfill; t += 256)
-        out[t] = -INFINITY;
+    if constexpr (FILL)
+        for (int64_t t = t0 + (tend - t0 + kBatch - 1) / kBatch * kBatch + threadIdx.x; t < tfill; t += 256)
+            out[t] = -INFINITY;
 }
 
 }  // namespace

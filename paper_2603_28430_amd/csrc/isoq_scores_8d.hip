@@ -4,9 +4,9 @@
 
 namespace isoq {
 
-ScoreKernel score_kernel_for_block8(int d, int bits, bool f16)
+ScoreKernel score_kernel_for_block8(int d, int bits, bool f16, bool fill)
 {
-    return pick_d<VAR_BLOCK8>(d, bits, f16);
+    return pick_d<VAR_BLOCK8>(d, bits, f16, fill);
 }
 
 }  // namespace isoq

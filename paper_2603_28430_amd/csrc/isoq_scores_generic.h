@@ -22,7 +22,7 @@ struct GenScoreShape {
 // Kernel (args: SArgs, GenScoreShape; grid (query head, chunk of
 // kScoreChunk positions, sequence), 256 threads, dynamic LDS
 // generic_score_lds(slots, variant) bytes) or nullptr.
-const void *generic_score_kernel_for(int variant, int bits, bool f16);
+const void *generic_score_kernel_for(int variant, int bits, bool f16, bool fill);
 
 inline size_t generic_score_lds(int slots, int variant)
 {

@@ -18,7 +18,8 @@
 namespace isoq {
 namespace {
 
-template <int VAR, int BITS, bool F16>
+// FILL: positions without a key get -inf.
+template <int VAR, int BITS, bool F16, bool FILL>
 __global__ __launch_bounds__(256) void generic_score_kernel(const SArgs a, const GenScoreShape g)
 {
     constexpr int SW = kGenSW<VAR>;
@@ -35,12 +36,12 @@ __global__ __launch_bounds__(256) void generic_score_kernel(const SArgs a, const
     len = min(len, a.max_len);
     len = min(len, (int64_t)a.max_blocks * a.block_size);
     const int64_t t0 = (int64_t)blockIdx.y * kScoreChunk;
-    // positions below tfill without a key get -inf (none unless asked for)
-    const int64_t tfill = a.fill ? min(t0 + (int64_t)kScoreChunk, a.max_len) : 0;
+    const int64_t tfill = min(t0 + (int64_t)kScoreChunk, a.max_len);   // (FILL) end of the chunk
     float *dst = a.scores + ((int64_t)s * a.n_q_heads + hq) * a.max_len;
     if (t0 >= len) {  // block-uniform: the whole workgroup leaves before the barrier
-        for (int64_t t = t0 + threadIdx.x; t < tfill; t += blockDim.x)
-            dst[t] = -INFINITY;
+        if constexpr (FILL)
+            for (int64_t t = t0 + threadIdx.x; t < tfill; t += blockDim.x)
+                dst[t] = -INFINITY;
         return;
     }
     const int set = a.n_sets == 1 ? 0 : h;
@@ -71,13 +72,14 @@ __global__ __launch_bounds__(256) void generic_score_kernel(const SArgs a, const
 
     const int64_t tend = min(t0 + (int64_t)kScoreChunk, len);
     const int32_t *table = a.block_table + (int64_t)s * a.max_blocks;
-    for (int64_t t = tend + threadIdx.x; t < tfill; t += blockDim.x)
-        dst[t] = -INFINITY;
+    if constexpr (FILL)
+        for (int64_t t = tend + threadIdx.x; t < tfill; t += blockDim.x)
+            dst[t] = -INFINITY;
     for (int64_t t = t0 + threadIdx.x; t < tend; t += blockDim.x) {
         const uint32_t bi = fast_div((uint32_t)t, a.div_block);
         const int32_t blk = table[bi];
         if (blk < 0 || blk >= a.n_blocks) {
-            if (t < tfill)
+            if constexpr (FILL)
                 dst[t] = -INFINITY;
             continue;
         }
@@ -102,32 +104,35 @@ __global__ __launch_bounds__(256) void generic_score_kernel(const SArgs a, const
 }
 
 template <int VAR, int BITS>
-const void *gen_score_dtype(bool f16)
+const void *gen_score_dtype(bool f16, bool fill)
 {
-    return f16 ? reinterpret_cast<const void *>(&generic_score_kernel<VAR, BITS, true>)
-               : reinterpret_cast<const void *>(&generic_score_kernel<VAR, BITS, false>);
+    if (fill)
+        return f16 ? reinterpret_cast<const void *>(&generic_score_kernel<VAR, BITS, true, true>)
+                   : reinterpret_cast<const void *>(&generic_score_kernel<VAR, BITS, false, true>);
+    return f16 ? reinterpret_cast<const void *>(&generic_score_kernel<VAR, BITS, true, false>)
+               : reinterpret_cast<const void *>(&generic_score_kernel<VAR, BITS, false, false>);
 }
 
 template <int VAR>
-const void *gen_score_bits(int bits, bool f16)
+const void *gen_score_bits(int bits, bool f16, bool fill)
 {
     switch (bits) {
-    case 2: return gen_score_dtype<VAR, 2>(f16);
-    case 3: return gen_score_dtype<VAR, 3>(f16);
-    case 4: return gen_score_dtype<VAR, 4>(f16);
+    case 2: return gen_score_dtype<VAR, 2>(f16, fill);
+    case 3: return gen_score_dtype<VAR, 3>(f16, fill);
+    case 4: return gen_score_dtype<VAR, 4>(f16, fill);
     }
     return nullptr;
 }
 
 }  // namespace
 
-const void *generic_score_kernel_for(int variant, int bits, bool f16)
+const void *generic_score_kernel_for(int variant, int bits, bool f16, bool fill)
 {
     switch (variant) {
-    case VAR_FULL: return gen_score_bits<VAR_FULL>(bits, f16);
-    case VAR_FAST: return gen_score_bits<VAR_FAST>(bits, f16);
-    case VAR_PLANAR2D: return gen_score_bits<VAR_PLANAR2D>(bits, f16);
-    case VAR_BLOCK8: return gen_score_bits<VAR_BLOCK8>(bits, f16);
+    case VAR_FULL: return gen_score_bits<VAR_FULL>(bits, f16, fill);
+    case VAR_FAST: return gen_score_bits<VAR_FAST>(bits, f16, fill);
+    case VAR_PLANAR2D: return gen_score_bits<VAR_PLANAR2D>(bits, f16, fill);
+    case VAR_BLOCK8: return gen_score_bits<VAR_BLOCK8>(bits, f16, fill);
     }
     return nullptr;
 }

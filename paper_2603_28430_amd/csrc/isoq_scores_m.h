@@ -220,7 +220,7 @@ __device__ __forceinline__ bool nonfinite(uint32_t bits) { return bits >= 0x7F80
 // qraw (if wanted), the largest magnitude of each head to mx and a flag to odd
 // where one is infinite or NaN.
 template <int VAR, int D>
-__device__ __forceinline__ void rotate_queries(const SArgs &a, int s, int h, int set, int G, float *qt, float *qraw,
+__device__ __forceinline__ void rotate_queries(const SMArgs &a, int s, int h, int set, int G, float *qt, float *qraw,
                                                uint32_t *mx, uint32_t *odd)
 {
     constexpr int LPQ = D / kCoordsPerLane, PL = kLanePL<VAR>;   // chunks per query, parameters per chunk
@@ -285,7 +285,7 @@ template <int D, int BITS, int QM>
 __device__ __forceinline__ void nonfinite_logits(const uint32_t *smem)
 {
     using S = ScoreMShape<D, BITS, QM>;
-    typedef const __attribute__((address_space(4))) SArgs KernArgs;
+    typedef const __attribute__((address_space(4))) SMArgs KernArgs;
     auto word = [&](int i) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)smem[i]); };
     KernArgs &a = *(KernArgs *)((uint64_t)word(kOddArgs + 1) << 32 | word(kOddArgs));
     constexpr int64_t RB = (int64_t)D * BITS / 8;
@@ -334,7 +334,7 @@ __device__ __forceinline__ void nonfinite_logits(const uint32_t *smem)
 }
 
 template <int D, int BITS, int QM, int HT, int NT, bool LOOP, bool MP>
-__global__ __launch_bounds__(256) void score_m_kernel(const SArgs a)
+__global__ __launch_bounds__(256) void score_m_kernel(const SMArgs a)
 {
     using S = ScoreMShape<D, BITS, QM>;
     constexpr int64_t RB = (int64_t)D * BITS / 8;    // record bytes
