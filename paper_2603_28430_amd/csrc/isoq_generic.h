@@ -152,19 +152,27 @@ struct CacheSrcRt {
 // 20.1 us (d = 100, 335,544 rows: 29.5 / 23.4 -> 22.9 / 17.5), quantize at 4
 // bits 36.2 -> 32.2 us (with the binary search of gen_ballot_encode4).
 template <int BITS, class Src>
-__device__ __forceinline__ uint32_t gen_read_slot(const Src &rec, int j, int nb)
+__device__ __forceinline__ uint32_t gen_read_slot_bytes(const Src &rec, int j, int nb)
 {
     auto byte = [&](int k) -> uint32_t { return k < nb ? (uint32_t)rec.template get<uint8_t>(k) : 0u; };
     if constexpr (BITS == 2) {
         return byte(j);
-    } else if constexpr (BITS == 4) {   // a slot's two bytes together where records are a whole number of half-words
-        return nb % 2 == 0 ? (uint32_t)rec.template get<uint16_t>(2 * j) : byte(2 * j) | (byte(2 * j + 1) << 8);
+    } else if constexpr (BITS == 4) {
+        return byte(2 * j) | byte(2 * j + 1) << 8;
     } else {
         // bits 12 j .. 12 j + 11: from byte 3 j / 2 on, an odd slot's in the
         // middle of it (one form for both, so that lanes do not diverge)
         const int k = (3 * j) >> 1;
-        return ((byte(k) | (byte(k + 1) << 8)) >> (4 * (j & 1))) & 0xFFFu;
+        return ((byte(k) | byte(k + 1) << 8) >> (4 * (j & 1))) & 0xFFFu;
     }
+}
+
+template <int BITS, class Src>
+__device__ __forceinline__ uint32_t gen_read_slot(const Src &rec, int j, int nb)
+{
+    if (BITS == 4 && nb % 2 == 0)   // a slot's two bytes together where records are a whole number of half-words
+        return rec.template get<uint16_t>(2 * j);
+    return gen_read_slot_bytes<BITS>(rec, j, nb);
 }
 
 // Write the bytes whose first bit lies in slot j's bit range; `next` is the

@@ -13,6 +13,8 @@
 // length, and keys whose block-table entry is out of range, are not written.
 #include "isoq_scores_generic.h"
 
+#include <type_traits>
+
 #include "isoq_generic.h"
 
 namespace isoq {
@@ -87,18 +89,31 @@ __global__ __launch_bounds__(256) void generic_score_kernel(const SArgs a, const
         const int64_t krow = ((int64_t)blk * a.n_kv_heads + h) * a.block_size + pos;
         // the record, piece-major in its head's block region
         const CacheSrcRt rec{a.k_idx + (krow - pos) * g.rec, pos, a.block_size, g.rec_lp, g.rec};
-        float acc = 0.f;
+        auto sum = [&](auto pairs) {
+            float acc = 0.f;
 #pragma unroll 4
-        for (int j = 0; j < g.slots; j++) {
-            uint32_t p;
-            if constexpr (SW == 8)
-                p = gen_read_slot8<BITS>(rec, j);
-            else
-                p = gen_read_slot<BITS>(rec, j, g.rec);
+            for (int j = 0; j < g.slots; j++) {
+                uint32_t p;
+                if constexpr (SW == 8)
+                    p = gen_read_slot8<BITS>(rec, j);
+                else if constexpr (decltype(pairs)::value)
+                    p = rec.template get<uint16_t>(2 * j);
+                else
+                    p = gen_read_slot_bytes<BITS>(rec, j, g.rec);
 #pragma unroll
-            for (int c = 0; c < SW; c++)
-                acc = fmaf(qt[SW * j + c], lev[(p >> (BITS * c)) & (K - 1)], acc);
-        }
+                for (int c = 0; c < SW; c++)
+                    acc = fmaf(qt[SW * j + c], lev[(p >> (BITS * c)) & (K - 1)], acc);
+            }
+            return acc;
+        };
+        // (4 bits: a slot's two bytes together where the record is a whole
+        // number of half-words, decided outside the sum: inside, 2-D keys of
+        // d = 90, whose record is not, took 25.1 us instead of 23.1)
+        float acc;
+        if (BITS == 4 && SW == 4 && g.rec % 2 == 0)
+            acc = sum(std::true_type{});
+        else
+            acc = sum(std::false_type{});
         dst[t] = a.k_rho[krow] * acc;
     }
 }
