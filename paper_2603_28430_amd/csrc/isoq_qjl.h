@@ -35,7 +35,8 @@ __global__ __launch_bounds__(WAVES * 64) void qjl_kernel(const KArgs a)
         __shared__ __align__(16) _Float16 lds_e[M::kBlockRows * M::kEStride];
         __shared__ uint32_t lds_sign[M::kBlockRows * M::kSignWords];
         __shared__ int64_t lds_crow[MODE == MODE_APPEND_QJL ? M::kBlockRows : 1];
-        M::run(a, lds_lut, lds_par, lds_e, lds_sign, lds_crow);
+        __shared__ int lds_pos[M::kStageRows ? M::kBlockRows : 1];
+        M::run(a, lds_lut, lds_par, lds_e, lds_sign, lds_crow, lds_pos);
     } else {
         __shared__ __align__(16) _Float16 lds_frag[QM * D];
         __shared__ float lds_levels[16];

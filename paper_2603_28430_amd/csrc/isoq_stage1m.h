@@ -113,6 +113,15 @@ struct Stage1M {
     // scattered over the token stride, so the row order gains no lines)
     static constexpr bool kPerm = !kAppend;
     static constexpr bool kEarly = !kQjl;
+    // 4-bit append with the sketch: the cache rows of a block's rows are worked
+    // out once per row, in LDS, and the barrier that they share with the lookup
+    // table comes after the loads of the rows.  (A slot per load in each lane
+    // took 16 registers, 86 in all, and so a CU's third block: d = 128, m =
+    // 128, 20,003 tokens x 8 heads 27.1 us, 23.3 with this, 24.0 for the blocks
+    // of several tiles that came before; 32,768 x 32: 165 / 131 / 145 us.  At 2
+    // and 3 bits the third block fits anyway: 4 to 8% faster up to 2,000
+    // tokens, 2 to 4% slower at d = 64 and 32,768 x 32.)
+    static constexpr bool kStageRows = kQjl && kAppend && kUseLut;
 
     // Geometry of load u for the lane of MFMA block b (= lane / 4) in wave w:
     // its chunk and its quad in the block's tile (block quad q holds
@@ -126,7 +135,7 @@ struct Stage1M {
 
     struct In {
         u32x4 raw;
-        int64_t slot;   // append modes: the token's cache slot
+        int64_t slot;   // append modes: the token's cache slot (not with kStageRows)
     };
 
     // Lane orders of a load.  A load instruction of the wave covers the same
@@ -272,7 +281,7 @@ struct Stage1M {
     static constexpr int kLdsWords = kLdsA + kLdsP > 0 ? kLdsA + kLdsP : 1;
 
     __device__ static void run(const KArgs &a, LutEntry *lds_lut, u32x4 *lds_par, _Float16 *lds_e = nullptr,
-                               uint32_t *lds_sign = nullptr, int64_t *lds_crow = nullptr)
+                               uint32_t *lds_sign = nullptr, int64_t *lds_crow = nullptr, int *lds_pos = nullptr)
     {
         constexpr int BT = WAVES * 64;
         const int lane = threadIdx.x & 63;
@@ -303,6 +312,17 @@ struct Stage1M {
         if constexpr (kQjl) {
             for (int i = threadIdx.x; i < kBlockRows * kSignWords; i += BT)
                 lds_sign[i] = 0u;
+            if constexpr (kStageRows) {
+                // cache row (-1: a skipped slot) and block position of every row
+                const int64_t row0 = tile0 * rows_per_tile;
+                for (int i = threadIdx.x; i < kBlockRows && row0 + i < nrows; i += BT) {
+                    bool ok;
+                    int pos;
+                    const int64_t orow = cache_slot(a, a.slots[row0 + i], blockIdx.x, ok, pos);
+                    lds_crow[i] = ok ? orow : -1;
+                    lds_pos[i] = pos;
+                }
+            }
         }
         if constexpr (kStage) {
             // the set's matrix pieces ([chunk][quad row][piece] in memory)
@@ -320,7 +340,7 @@ struct Stage1M {
                 }
             }
         }
-        if constexpr (kStage || kUseLut)   // (the sketch's first tile has a barrier of its own)
+        if constexpr (kStage || (kUseLut && !kStageRows))   // (the sketch has a barrier of its own)
             __syncthreads();
 
         // 2. the lane's matrix rows (quad row qi) of its SPQ chunks (the
@@ -356,13 +376,28 @@ struct Stage1M {
         if constexpr (kQjl) {
             // encode (errors to LDS), project together, write the signs
             const int64_t row0 = tile0 * rows_per_tile;
-            __syncthreads();   // the cleared sign records
+            const bool some = row0 + 4 * first_quad < nrows;
+            // one barrier: the cleared sign records, and with kStageRows the
+            // lookup table and the cache rows
+            if constexpr (!kStageRows)
+                __syncthreads();
             if (row0 + rows_per_tile <= nrows) {
                 load<false>(a, row0, nrows, b, qi, w, buf, roffs);
-                process<false>(a, Am, lds_par, lev, thr, lds_lut, row0, nrows, b, qi, w, lds_e, lds_crow, buf, roffs);
-            } else if (row0 + 4 * first_quad < nrows) {
+                if constexpr (kStageRows)
+                    __syncthreads();
+                process<false>(a, Am, lds_par, lev, thr, lds_lut, row0, nrows, b, qi, w, lds_e, lds_crow, lds_pos,
+                               buf, roffs);
+            } else if constexpr (kStageRows) {
+                if (some)
+                    load<true>(a, row0, nrows, b, qi, w, buf, roffs);
+                __syncthreads();
+                if (some)
+                    process<true>(a, Am, lds_par, lev, thr, lds_lut, row0, nrows, b, qi, w, lds_e, lds_crow, lds_pos,
+                                  buf, roffs);
+            } else if (some) {
                 load<true>(a, row0, nrows, b, qi, w, buf, roffs);
-                process<true>(a, Am, lds_par, lev, thr, lds_lut, row0, nrows, b, qi, w, lds_e, lds_crow, buf, roffs);
+                process<true>(a, Am, lds_par, lev, thr, lds_lut, row0, nrows, b, qi, w, lds_e, lds_crow, lds_pos, buf,
+                              roffs);
             }
             half8 F[kTilesPerWave][D / 32];
             load_projection(a, set, w, F);
@@ -376,10 +411,12 @@ struct Stage1M {
                 return;
             if (row0 + rows_per_tile <= nrows) {
                 load<false>(a, row0, nrows, b, qi, w, buf, roffs);
-                process<false>(a, Am, lds_par, lev, thr, lds_lut, row0, nrows, b, qi, w, nullptr, nullptr, buf, roffs);
+                process<false>(a, Am, lds_par, lev, thr, lds_lut, row0, nrows, b, qi, w, nullptr, nullptr, nullptr, buf,
+                               roffs);
             } else {
                 load<true>(a, row0, nrows, b, qi, w, buf, roffs);
-                process<true>(a, Am, lds_par, lev, thr, lds_lut, row0, nrows, b, qi, w, nullptr, nullptr, buf, roffs);
+                process<true>(a, Am, lds_par, lev, thr, lds_lut, row0, nrows, b, qi, w, nullptr, nullptr, nullptr, buf,
+                               roffs);
             }
         }
     }
@@ -405,7 +442,7 @@ struct Stage1M {
                 buf[u].raw = fetch(a, row0, rl, row_chunk_of(u, lane));
             else
                 buf[u].raw = fetch(a, row0, r, chunk_of(u, b));
-            if constexpr (kAppend)
+            if constexpr (kAppend && !kStageRows)
                 buf[u].slot = (a.slots + row0)[r];
         }
     }
@@ -414,7 +451,7 @@ struct Stage1M {
     __device__ static __forceinline__ void process(const KArgs &a, const u32x4 (*Am)[PB], const u32x4 *lds_par,
                                                    const float *lev, const float *thr, const LutEntry *lut,
                                                    int64_t row0, int64_t nrows, int b, int qi, int w, _Float16 *eq,
-                                                   int64_t *crq, In *buf, const int *roffs)
+                                                   int64_t *crq, const int *posq, In *buf, const int *roffs)
     {
         const int lane = threadIdx.x & 63;
         __builtin_amdgcn_sched_barrier(0);
@@ -466,7 +503,7 @@ struct Stage1M {
                                 // the row of the error tile (a constant step
                                 // per load; at d = 256 that form cost 10%)
                                 C <= 16 ? 4 * bquad_of(u0 + h, b, w) + qi : roffs[u0 + h],
-                                kEarly ? yy[u0 + h] : ylate, rl, row_chunk_of(u0 + h, lane), crq, crow);
+                                kEarly ? yy[u0 + h] : ylate, rl, row_chunk_of(u0 + h, lane), crq, posq, crow);
             }
             if constexpr (kQjl) {
                 // gamma = rho ||e|| over the row's chunks (T is orthogonal:
@@ -501,7 +538,8 @@ struct Stage1M {
                                                     const float *lev, const float *thr, const LutEntry *lut,
                                                     const In &in, int64_t row0, int roff, int c, float rho,
                                                     float rho_e, _Float16 *eq, int erow, const float *y_in,
-                                                    int rl_roff, int rl_chunk, int64_t *crq, int64_t &crow)
+                                                    int rl_roff, int rl_chunk, int64_t *crq, const int *posq,
+                                                    int64_t &crow)
     {
         float y[8], m[8], yq[8];
 #pragma unroll
@@ -535,12 +573,19 @@ struct Stage1M {
             if constexpr (kAppend) {
                 bool ok;
                 int pos;
-                const int64_t orow = cache_slot(a, in.slot, blockIdx.x, ok, pos);
+                int64_t orow;
+                if constexpr (kStageRows) {
+                    orow = crq[roff];
+                    pos = posq[roff];
+                    ok = orow >= 0;
+                } else {
+                    orow = cache_slot(a, in.slot, blockIdx.x, ok, pos);
+                }
                 store_bits(cache_rec<RECB>(a, orow, pos), c, p, ok);
                 if (ok && c == 0)
                     a.norms_out[orow] = rho;
                 crow = ok ? orow : -1;
-                if constexpr (kQjl) {
+                if constexpr (kQjl && !kStageRows) {
                     if (c == 0)
                         crq[erow] = crow;
                 }

@@ -108,6 +108,19 @@ def test_append_qjl_decode_step_and_skipped_slots():
              seed=6, skip_every=97)
 
 
+@pytest.mark.parametrize("d,m", [(64, 64), (64, 128), (128, 64), (128, 128), (256, 64)])
+@pytest.mark.parametrize("extra", [-1, 0, 1])
+def test_append_qjl_4bit_tiles(d, m, extra):
+    """4 bits, around the end of a block's tile (16,384 coordinates of a head:
+    its cache rows are staged per tile): one token, a whole tile and its
+    neighbours, skipped slots in both, an odd block size."""
+    tile = 16384 // d
+    run_case("full" if extra else "fast", d, 4, m, "f16", n_tokens=max(1, tile + extra if extra >= 0 else 1), n_heads=3,
+             block_size=7, n_blocks=60, n_sets=3, seed=d + m + extra)
+    run_case("fast", d, 4, m, "f16", n_tokens=2 * tile + extra, n_heads=2, block_size=16, n_blocks=80, n_sets=1,
+             seed=d + m + extra, skip_every=9)
+
+
 def test_append_qjl_then_corrected_scores():
     """Keys appended with the sketch, then scored with the correction: the
     logit error against <q, x> averages to zero (residual signs are
