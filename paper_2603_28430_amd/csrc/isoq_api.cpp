@@ -26,6 +26,7 @@ struct isoq_params {
     isoq::LevelDigits lv;             // levels as digits (the first set)
     size_t lv_offset;               // floats from dparams to the further sets
     int n_pass;                     // sets in all
+    bool wide;                      // the logits need all sets and digit products
 };
 
 struct isoq_sketch {
@@ -413,7 +414,7 @@ isoq_status isoq_params_init(isoq_params **out, int variant, int d, int bits, in
     // device with the rest
     std::vector<LevelDigits> lv;
     try {
-        build_level_digits(bits, p->levels, lv);
+        p->wide = !build_level_digits(bits, p->levels, lv);
         while (layout.size() % 4)
             layout.push_back(0.f);
         p->lv = lv[0];
@@ -784,7 +785,7 @@ isoq_status kv_scores(const isoq_params *pk, const isoq_sketch *sk, int dtype, c
                                  block_table, max_blocks_per_seq, seq_lens, scale, scores, max_len, max_pos,
                                  fill, stream);
     const bool tables = score_by_tables(pk->d, pk->bits, group);
-    const ScoreKernel kern = !tables ? score_m_kernel_for(pk->d, pk->bits, group, sk ? sk->m : 0, pk->n_pass > 1)
+    const ScoreKernel kern = !tables ? score_m_kernel_for(pk->d, pk->bits, group, sk ? sk->m : 0, pk->wide)
                              : sk    ? score_qjl_kernel_for(pk->variant, pk->d, pk->bits, dtype == ISOQ_F16, sk->m, fill)
                                      : score_kernel_for(pk->variant, pk->d, pk->bits, dtype == ISOQ_F16, fill);
     if (!kern.fn)

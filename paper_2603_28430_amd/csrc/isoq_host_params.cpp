@@ -457,7 +457,7 @@ void build_mfma_params(int variant, int d, const float *set_layout, uint16_t *ou
 }
 
 // ------------------------------------------------------- magnitude lookup table
-void build_level_digits(int bits, const float *levels, std::vector<LevelDigits> &out)
+bool build_level_digits(int bits, const float *levels, std::vector<LevelDigits> &out)
 {
     // magnitudes m_k of the positive half; an integer n stands for n q, or at
     // 4 bits for (n + half) q, half = (1 + 256 + 256^2) / 2, so that the
@@ -474,6 +474,7 @@ void build_level_digits(int bits, const float *levels, std::vector<LevelDigits> 
         per_level[k] = level[k] > 0 ? 1.0 / level[k] : 0.0;
     }
     out.clear();
+    long smallest = 0;   // integer of the first set
     for (;;) {
         double big = 0;
         for (int k = 0; k < H; k++)
@@ -501,6 +502,8 @@ void build_level_digits(int bits, const float *levels, std::vector<LevelDigits> 
         for (int k = 0; k < H; k++) {
             const long n = std::lrint(rest[k] / q - half);
             rest[k] -= ((double)n + half) * q;
+            if (out.empty() && k == 0)
+                smallest = std::lrint((double)n + half);
             for (int sign = 0; sign < (bits == 4 ? 1 : 2); sign++) {
                 long v = sign ? -n : n;
                 const int at = bits == 4 ? k : sign ? H - 1 - k : H + k;   // 4 bits: by magnitude
@@ -521,7 +524,7 @@ void build_level_digits(int bits, const float *levels, std::vector<LevelDigits> 
         for (int k = 0; k < H; k++)
             done = done && std::fabs(rest[k]) <= std::ldexp(level[k], -23);
         if (done || out.size() == 8)
-            return;
+            return out.size() == 1 && smallest >= 1 << 17;
     }
 }
 

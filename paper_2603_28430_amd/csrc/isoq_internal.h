@@ -183,9 +183,9 @@ ScoreKernel score_qjl_kernel_for(int variant, int d, int bits, bool f16, int m, 
 
 // The matrix-core logit kernel (isoq_scores_m.h, any variant and query type)
 // for width d, bits, query heads per key head and m sketch bits (0: none) and
-// the dynamic LDS bytes it needs; passes: levels held in several sets of
-// digits.
-ScoreKernel score_m_kernel_for(int d, int bits, int group, int m, bool passes);
+// the dynamic LDS bytes it needs; wide: levels held in several sets of digits
+// or summed with every digit product (build_level_digits).
+ScoreKernel score_m_kernel_for(int d, int bits, int group, int m, bool wide);
 
 // Paged caches (isoq_kv_append, isoq_kv_scores) hold a head's records of
 // one cache block piece-major: a record of R bytes is cut into pieces of
@@ -348,8 +348,12 @@ bool build_magnitude_lut(int H, const double *tau, const double *lev, double *in
                          std::vector<LutEntry> &lut);
 // The levels (symmetric, ascending, 2^bits of them) as digits, one set or,
 // where that leaves a level off by more than 2^-23 of itself, further sets for
-// the remainders.
-void build_level_digits(int bits, const float *levels, std::vector<LevelDigits> &out);
+// the remainders.  Returns whether the kernel's short sum does for them: one
+// set, and no level's integer below 2^17 (of 2^23), where the digit products
+// that the sum leaves out, 30 units of 256^2 per coordinate in the root mean
+// square, come to 2^-24 of those that it has (a rotated query whose largest
+// coordinate is four times its root mean square).
+bool build_level_digits(int bits, const float *levels, std::vector<LevelDigits> &out);
 // Lloyd-Max levels for N(0, sigma^2) (ascending, symmetrised).
 bool lloyd_levels(int bits, double sigma, int iters, double *levels);
 // Seeded raw draws (Philox4x32-10 + Box-Muller), layout of the public header.

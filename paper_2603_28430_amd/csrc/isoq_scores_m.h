@@ -18,7 +18,8 @@
 // (4 bits: c_k = quantum (int + (1 + 256 + 256^2) / 2), so that a level's
 // mirror image is the complement of its digits).  The quantum is searched so
 // that the integers hit the levels (build_level_digits); a codebook that one
-// set of digits does not hold to 2^-23 of each level takes further passes over
+// set of digits does not hold to 2^-23 of each level, or whose smallest level is
+// far below the largest, is `wide` (MP): every digit product, and passes over
 // the residual levels.  Against 64 bits the logits are off by 5e-8 of their
 // rms; the fp32 lookup tables that this replaces were off by 1.3e-7.
 //
@@ -771,13 +772,19 @@ __global__ __launch_bounds__(256) void score_m_kernel(const SMArgs a)
                     }
 #pragma unroll
                     for (int nt = 0; nt < NT; nt++) {
-                        // sum of 256^(5 - t - j) acc[t][j], in units of 256^2
-                        // (the terms below them are under 2^-32 of the largest)
+                        // sum of 256^(5 - t - j) acc[t][j], in units of 256^2.
+                        // (The terms below them are left out: 128.25 per
+                        // coordinate at most, 2^-28 of the largest product,
+                        // 30 in the root mean square; with wide codebooks they
+                        // are all that some levels have.)
                         const i32x4 *d = acc[nt];
                         const int w01 = (d[0][0] << 8) + d[0][1] + d[1][0];
                         const int w2 = d[0][2] + d[1][1] + d[2][0];
                         const int w3 = d[0][3] + d[1][2] + d[2][1];
-                        const float f = fmaf((float)w01, 65536.f, fmaf((float)w2, 256.f, (float)w3));
+                        float f = (float)w3;
+                        if constexpr (MP)
+                            f += fmaf((float)(d[1][3] + d[2][2]), 0x1p-8f, (float)d[2][3] * 0x1p-16f);
+                        f = fmaf((float)w01, 65536.f, fmaf((float)w2, 256.f, f));
                         val[nt] = !MP ? f : pass == 0 ? f * quantum : fmaf(f, quantum, val[nt]);
                     }
                     if (!MP || ++pass >= a.n_pass)   // uniform

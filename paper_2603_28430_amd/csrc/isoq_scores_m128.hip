@@ -4,9 +4,9 @@
 
 namespace isoq {
 
-ScoreKernel score_m_kernel_m128(int d, int bits, int group, bool passes)
+ScoreKernel score_m_kernel_m128(int d, int bits, int group, bool wide)
 {
-    return score_m_d<128>(d, bits, group, passes);
+    return score_m_d<128>(d, bits, group, wide);
 }
 
 }  // namespace isoq

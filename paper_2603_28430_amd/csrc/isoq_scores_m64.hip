@@ -4,9 +4,9 @@
 
 namespace isoq {
 
-ScoreKernel score_m_kernel_m64(int d, int bits, int group, bool passes)
+ScoreKernel score_m_kernel_m64(int d, int bits, int group, bool wide)
 {
-    return score_m_d<64>(d, bits, group, passes);
+    return score_m_d<64>(d, bits, group, wide);
 }
 
 }  // namespace isoq

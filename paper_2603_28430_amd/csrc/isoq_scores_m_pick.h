@@ -12,13 +12,13 @@ namespace {
 // Heads per tile and tiles per pass: two heads (up to d = 256; the two copies
 // of their query digits take d / 8 registers) share the row groups of the
 // matrix instruction between 16-key groups; up to four take one tile; more
-// loop, eight at a time up to d = 192.
+// loop, eight at a time up to d = 192.  Wide codebooks loop, four at a time.
 template <int D, int BITS, int QM>
-ScoreKernel score_m_entry(int group, bool passes)
+ScoreKernel score_m_entry(int group, bool wide)
 {
     using S = ScoreMShape<D, BITS, QM>;
     const size_t lds = sizeof(uint32_t) * (kOddWords + (size_t)group * S::head_words());
-    if (passes)
+    if (wide)
         return {reinterpret_cast<const void *>(&score_m_kernel<D, BITS, QM, 4, 1, true, true>), lds};
     if constexpr (D <= 256) {
         if (group == 2)
@@ -30,32 +30,32 @@ ScoreKernel score_m_entry(int group, bool passes)
 }
 
 template <int D, int QM>
-ScoreKernel score_m_bits(int bits, int group, bool passes)
+ScoreKernel score_m_bits(int bits, int group, bool wide)
 {
     switch (bits) {
-    case 2: return score_m_entry<D, 2, QM>(group, passes);
-    case 3: return score_m_entry<D, 3, QM>(group, passes);
-    case 4: return score_m_entry<D, 4, QM>(group, passes);
+    case 2: return score_m_entry<D, 2, QM>(group, wide);
+    case 3: return score_m_entry<D, 3, QM>(group, wide);
+    case 4: return score_m_entry<D, 4, QM>(group, wide);
     }
     return {nullptr, 0};
 }
 
 template <int QM>
-ScoreKernel score_m_d(int d, int bits, int group, bool passes)
+ScoreKernel score_m_d(int d, int bits, int group, bool wide)
 {
     switch (d) {
-    case 64: return score_m_bits<64, QM>(bits, group, passes);
-    case 80: return score_m_bits<80, QM>(bits, group, passes);
-    case 96: return score_m_bits<96, QM>(bits, group, passes);
-    case 128: return score_m_bits<128, QM>(bits, group, passes);
-    case 160: return score_m_bits<160, QM>(bits, group, passes);
-    case 192: return score_m_bits<192, QM>(bits, group, passes);
+    case 64: return score_m_bits<64, QM>(bits, group, wide);
+    case 80: return score_m_bits<80, QM>(bits, group, wide);
+    case 96: return score_m_bits<96, QM>(bits, group, wide);
+    case 128: return score_m_bits<128, QM>(bits, group, wide);
+    case 160: return score_m_bits<160, QM>(bits, group, wide);
+    case 192: return score_m_bits<192, QM>(bits, group, wide);
     }
     if constexpr (QM < 128) {
         if (d == 256)
-            return score_m_bits<256, QM>(bits, group, passes);
+            return score_m_bits<256, QM>(bits, group, wide);
         if (d == 512)
-            return score_m_bits<512, QM>(bits, group, passes);
+            return score_m_bits<512, QM>(bits, group, wide);
     }
     return {nullptr, 0};
 }

@@ -1,5 +1,5 @@
 // Prints, for each codebook read from stdin (bits, then 2^bits levels), the
-// number of digit sets and the values that the digits stand for, level by
+// number of digit sets, whether the short sum does, and the values that the digits stand for, level by
 // level, as the logit kernel sums them.
 #include <cmath>
 #include <cstdio>
@@ -17,8 +17,8 @@ int main()
             if (std::scanf("%f", lev + k) != 1)
                 return 1;
         std::vector<isoq::LevelDigits> sets;
-        isoq::build_level_digits(bits, lev, sets);
-        std::printf("%zu", sets.size());
+        const bool narrow = isoq::build_level_digits(bits, lev, sets);
+        std::printf("%zu %d", sets.size(), (int)narrow);
         for (int k = 0; k < K; k++) {
             double v = 0;
             for (const isoq::LevelDigits &s : sets) {

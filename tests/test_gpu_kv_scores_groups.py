@@ -65,26 +65,36 @@ def test_scores_sketch_groups(d, m, bits, group):
                     seq_lens=[321, 64], seed=d + m + group)
 
 
-@pytest.mark.parametrize("bits,ratio", [(2, 3e4), (3, 1e3), (4, 200.0), (4, 40.0)])
-def test_scores_groups_wide_codebook(monkeypatch, bits, ratio):
-    """Levels spread over `ratio`: further sets of digits hold the small ones,
-    also for a key made of small levels only."""
+def wide_codebook(bits, ratio):
+    """Levels spread over `ratio`."""
     k = 1 << (bits - 1)
     pos = 0.1 * ratio ** (np.arange(k) / (k - 1) - 1.0)
-    levels = np.concatenate([-pos[::-1], pos]).astype(np.float32).astype(np.float64)
+    return np.concatenate([-pos[::-1], pos]).astype(np.float32).astype(np.float64)
+
+
+@pytest.mark.parametrize("bits,ratio", [(2, 3e4), (2, 1e6), (3, 1e3), (3, 1e5), (4, 200.0), (4, 40.0)])
+@pytest.mark.parametrize("group", [2, 3, 9])
+def test_scores_groups_wide_codebook(monkeypatch, bits, ratio, group):
+    """Levels that one set of digits does not hold: further sets hold them, also
+    for a key made of small levels only."""
+    k = 1 << (bits - 1)
+    levels = wide_codebook(bits, ratio)
     monkeypatch.setattr(oracle, "codebook", lambda b, d: levels)
-    plain.run_case("full", 128, bits, "f16", n_seqs=1, n_q=6, n_kv=2, bs=16, seq_lens=[300], seed=bits)
+    plain.run_case("full", 128, bits, "f16", n_seqs=1, n_q=2 * group, n_kv=2, bs=16, seq_lens=[300], seed=bits)
     small = lambda s, h, n: (np.full((n, 128), k, np.uint8), np.ones(n, np.float32))  # noqa: E731
-    plain.run_case("full", 128, bits, "f32", n_seqs=1, n_q=6, n_kv=2, bs=16, seq_lens=[70], seed=bits, keys=small)
+    plain.run_case("full", 128, bits, "f32", n_seqs=1, n_q=2 * group, n_kv=2, bs=16, seq_lens=[70], seed=bits,
+                   keys=small)
 
 
-@pytest.mark.parametrize("d", [64, 128, 192, 256])
-@pytest.mark.parametrize("bits", [2, 3, 4])
-def test_scores_groups_small_level_keys(d, bits):
+@pytest.mark.parametrize("d,bits,ratio", [(d, b, None) for d in (64, 128, 192, 256) for b in (2, 3, 4)] +
+                         [(128, 2, 1e6), (128, 3, 1e5), (64, 4, 200.0)])
+def test_scores_groups_small_level_keys(monkeypatch, d, bits, ratio):
     """Keys made of the two smallest levels +-c only: their logits are exactly
     proportional to c, so they are off by what c is off (2^-23 of itself at
     most) and by the fp32 roundings of the query, of the sum and of its two
     factors (2^-24 each, 2^-22 together)."""
+    if ratio:
+        monkeypatch.setattr(oracle, "codebook", lambda b, d: wide_codebook(bits, ratio))
     p, rot, levels = plain.make("fast", d, bits, 2)
     half = 1 << (bits - 1)
     rng = np.random.default_rng(d + bits)
@@ -100,7 +110,7 @@ def test_scores_groups_small_level_keys(d, bits):
     assert err <= 2.0 ** -23 + 2.0 ** -22, err * 2.0 ** 24
 
 
-@pytest.mark.parametrize("ratio", [None, 1e3])
+@pytest.mark.parametrize("ratio", [None, 1e5])
 def test_scores_groups_codebook_scale(ratio):
     """Codebooks near the ends of the range of floats (one and several sets of
     digits): the logits of a codebook times a power of two are the logits times
@@ -108,8 +118,7 @@ def test_scores_groups_codebook_scale(ratio):
     d, bits = 128, 3
     levels = np.float32(oracle.codebook(bits, d)).astype(np.float64)
     if ratio:
-        pos = 0.1 * ratio ** (np.arange(4) / 3 - 1.0)
-        levels = np.concatenate([-pos[::-1], pos]).astype(np.float32).astype(np.float64)
+        levels = wide_codebook(bits, ratio)
     rng = np.random.default_rng(9)
     cache = plain.Cache(rng, d, bits, 1, 2, 16, [200])
     rec, rho, table, lens = cache.device()

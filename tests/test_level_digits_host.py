@@ -39,8 +39,10 @@ def test_level_digits(tmp_path):
     lines = out.strip().splitlines()
     assert len(lines) == len(books)
     for line, (b, c, sets) in zip(lines, books):
-        n, *vals = line.split()
+        n, narrow, *vals = line.split()
         vals, ref = np.array(vals, float), np.float32(c).astype(float)
         assert 1 <= int(n) < 8 and (sets is None or int(n) == sets), (b, n)
         assert np.all(np.abs(vals - ref) <= 2.0 ** -23 * np.abs(ref)), (b, vals / ref - 1)
         assert np.array_equal(vals, -vals[::-1])
+        # the short sum: the Lloyd-Max codebooks, not those of distant levels
+        assert int(narrow) if sets else not (int(narrow) and ref[-1] > 64 * ref[len(ref) // 2])
