@@ -12,12 +12,19 @@ namespace {
 // Heads per tile and tiles per pass: two heads (up to d = 256; the two copies
 // of their query digits take d / 8 registers) share the row groups of the
 // matrix instruction between 16-key groups; up to four take one tile; more
-// loop, eight at a time up to d = 192.  Wide codebooks loop, four at a time.
+// loop, eight at a time up to d = 192.  Wide codebooks loop,
+// four at a time, except for two heads (two sets, d = 128, 3 bits, 8 x 8 key
+// heads, 8,192 keys: 18.0 us in the loop, 15.8 by pairs; 14.7 with lookup
+// tables.  One set: 12.7 -> 11.2 us).
 template <int D, int BITS, int QM>
 ScoreKernel score_m_entry(int group, bool wide)
 {
     using S = ScoreMShape<D, BITS, QM>;
     const size_t lds = sizeof(uint32_t) * (kOddWords + (size_t)group * S::head_words());
+    if constexpr (D <= 256) {
+        if (wide && group == 2)
+            return {reinterpret_cast<const void *>(&score_m_kernel<D, BITS, QM, 2, 1, false, true>), lds};
+    }
     if (wide)
         return {reinterpret_cast<const void *>(&score_m_kernel<D, BITS, QM, 4, 1, true, true>), lds};
     if constexpr (D <= 256) {
