@@ -413,10 +413,10 @@ def isoq_kv_scores(pk: Params, q, k_idx, k_rho, block_table, seq_lens, scale: fl
                 or k_gamma.shape != cache[:3] or k_gamma.dtype != torch.float32):
             raise ValueError("k_signs [n_blocks, n_kv_heads, block_size, m/8] uint8, k_gamma like k_rho")
         _placed(q, (q, k_idx, k_rho, block_table, seq_lens, scores, k_signs, k_gamma))
-    cache_args = (n_blocks, block_size, block_table.data_ptr(), max_blocks, seq_lens.data_ptr(), float(scale),
-                  scores.data_ptr(), int(max_len), _stream_ptr(stream))
     head_args = (_dtype_code(q.dtype), q.data_ptr(), n_seqs, n_q_heads, n_kv_heads, k_idx.data_ptr(),
                  k_rho.data_ptr())
+    cache_args = (n_blocks, block_size, block_table.data_ptr(), max_blocks, seq_lens.data_ptr(), float(scale),
+                  scores.data_ptr(), int(max_len), _stream_ptr(stream))
     if filled:
         st = lib.isoq_kv_scores_filled(pk.handle, None if sketch is None else sketch.handle, *head_args,
                                        _ptr(k_signs), _ptr(k_gamma), *cache_args)

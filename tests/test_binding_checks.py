@@ -15,7 +15,7 @@ from paper_2603_28430_amd import isoquant as binding
 
 
 _LAUNCHES = {"isoq_roundtrip", "isoq_quantize", "isoq_dequantize", "isoq_kv_append", "isoq_kv_scores",
-             "isoq_quantize_qjl", "isoq_kv_append_qjl", "isoq_kv_scores_qjl"}
+             "isoq_kv_scores_filled", "isoq_quantize_qjl", "isoq_kv_append_qjl", "isoq_kv_scores_qjl"}
 
 
 class _NoLaunch:
@@ -118,3 +118,34 @@ def test_kv_calls_check_placement(cpu_as_device):
     lens = torch.zeros(1, dtype=torch.int32)
     _raises(lambda: iq.isoq_kv_scores(p, q, cache, rho, table, lens.to("meta")))
     _raises(lambda: iq.isoq_kv_scores(p, q, cache.to("meta"), rho, table, lens))
+
+
+def test_kv_scores_checks(cpu_as_device):
+    """With a caller's buffer, with one allocated by the binding (another entry
+    of the library) and with a sketch."""
+    p = _params()
+    sk = iq.Sketch(0, p, 64)
+    q = torch.zeros((1, 4, 128), dtype=torch.float16)
+    cache = torch.zeros((2, 2, 16, p.record_bytes), dtype=torch.uint8)
+    rho = torch.zeros((2, 2, 16), dtype=torch.float32)
+    table = torch.zeros((1, 2), dtype=torch.int32)
+    lens = torch.zeros(1, dtype=torch.int32)
+    out = torch.zeros((1, 4, 32), dtype=torch.float32)
+    sg = torch.zeros((2, 2, 16, 8), dtype=torch.uint8)
+    good = dict(q=q, k_idx=cache, k_rho=rho, block_table=table, seq_lens=lens)
+    bad = [("q", q.to("meta")), ("q", q[..., :64]), ("q", q.to(torch.bfloat16)), ("k_idx", cache.to("meta")),
+           ("k_idx", cache[..., :40]), ("k_rho", rho.to("meta")), ("k_rho", rho[:, :, :8]),
+           ("block_table", table.to("meta")), ("block_table", table.long()), ("block_table", table.repeat(2, 1)),
+           ("seq_lens", lens.to("meta")), ("seq_lens", lens.long()), ("k_rho", rho.transpose(0, 1).contiguous().transpose(0, 1))]
+    for name, t in bad:
+        for more in (dict(), dict(scores=out), dict(sketch=sk, k_signs=sg, k_gamma=rho),
+                     dict(scores=out, sketch=sk, k_signs=sg, k_gamma=rho)):
+            kw = dict(good, **{name: t}, **more)
+            _raises(lambda: iq.isoq_kv_scores(p, **kw))
+    for t in (out.to("meta"), out[:, :, :31], out.to(torch.float64), torch.zeros((1, 32, 4)).transpose(1, 2)):
+        _raises(lambda: iq.isoq_kv_scores(p, **good, max_len=32, scores=t))
+        _raises(lambda: iq.isoq_kv_scores(p, **good, max_len=32, scores=t, sketch=sk, k_signs=sg, k_gamma=rho))
+    for signs, gamma in ((sg.to("meta"), rho), (sg, rho.to("meta")), (sg[..., :4], rho), (sg.int(), rho),
+                         (sg, rho.half()), (None, rho), (sg, None)):
+        for more in (dict(), dict(scores=out)):
+            _raises(lambda: iq.isoq_kv_scores(p, **good, **more, sketch=sk, k_signs=signs, k_gamma=gamma))
