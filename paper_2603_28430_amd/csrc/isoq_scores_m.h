@@ -339,6 +339,7 @@ __global__ __launch_bounds__(256) void score_m_kernel(const SMArgs a)
 {
     using S = ScoreMShape<D, BITS, QM>;
     constexpr int64_t RB = (int64_t)D * BITS / 8;    // record bytes
+    static_assert(HT == 2 || HT == 4, "heads per instruction");
     constexpr int RG = 4 / HT;                       // 16-key groups per accumulator
     constexpr int HPS = HT * NT;                     // heads per pass over a batch's digits
     constexpr int QP = BITS == 4 ? 29 : 30;          // query integers below 2^QP (4 bits: digits of twice them)
@@ -799,12 +800,10 @@ __global__ __launch_bounds__(256) void score_m_kernel(const SMArgs a)
                 }
                 // the lane's key: 16 (RG st + rgl) + col of the wave's 64
                 const int kk = 16 * (RG * st + rgl) + col;
-                float rho = rho_own, gam = gam_own;
-                if constexpr (HT > 1) {
-                    rho = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * kk, __float_as_int(rho)));
-                    if constexpr (QM > 0)
-                        gam = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * kk, __float_as_int(gam)));
-                }
+                const float rho = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * kk, __float_as_int(rho_own)));
+                float gam = 0.f;
+                if constexpr (QM > 0)
+                    gam = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * kk, __float_as_int(gam_own)));
                 const int t = tb + kk;
 #pragma unroll
                 for (int nt = 0; nt < NT; nt++) {

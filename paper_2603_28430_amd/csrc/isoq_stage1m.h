@@ -682,13 +682,9 @@ struct Stage1M {
     __device__ static __forceinline__ void load_projection(const KArgs &a, int64_t set, int w,
                                                            half8 (*F)[D / 32])
     {
-        // an offset the compiler cannot see through (it is zero): the loads
-        // stay in the tile loop
-        int o = 0;
-        asm volatile("" : "+s"(o));
 #pragma unroll
         for (int t = 0; t < kTilesPerWave; t++) {
-            const half8 *f = o + reinterpret_cast<const half8 *>(a.qjl_frag + set * (int64_t)(QM * D)) +
+            const half8 *f = reinterpret_cast<const half8 *>(a.qjl_frag + set * (int64_t)(QM * D)) +
                              (w % NT + t * WAVES) * (D / 32) * 64 + (threadIdx.x & 63);
 #pragma unroll
             for (int ks = 0; ks < D / 32; ks++)
@@ -738,10 +734,9 @@ struct Stage1M {
         }
     }
 
-    // The signs of the wave's share of the block's rows (consecutive rows),
-    // cleared for the next tile.
-    __device__ static __forceinline__ void write_signs(const KArgs &a, uint32_t *sign, const int64_t *crow, int64_t row0,
-                                                       int64_t nrows, int w)
+    // The signs of the wave's share of the block's rows (consecutive rows).
+    __device__ static __forceinline__ void write_signs(const KArgs &a, const uint32_t *sign, const int64_t *crow,
+                                                       int64_t row0, int64_t nrows, int w)
     {
         const int lane = threadIdx.x & 63;
 #pragma unroll
@@ -749,7 +744,6 @@ struct Stage1M {
             const int i = i0 + lane, r = w * RT + i / kSignWords, wd = i % kSignWords;
             if (i < RT * kSignWords) {
                 const uint32_t v = sign[r * kSignWords + wd];
-                sign[r * kSignWords + wd] = 0u;
                 if (row0 + r < nrows) {
                     int64_t orow = row0 + r;
                     if constexpr (kAppend)
