@@ -410,21 +410,27 @@ isoq_status isoq_params_init(isoq_params **out, int variant, int d, int bits, in
         layout.insert(layout.end(), f, f + mf.size() / 2);
     }
 
-    // the levels as digits for the logits; sets after the first go to the
-    // device with the rest
-    std::vector<LevelDigits> lv;
-    try {
-        p->wide = !build_level_digits(bits, p->levels, lv);
-        while (layout.size() % 4)
-            layout.push_back(0.f);
-        p->lv = lv[0];
-        p->n_pass = (int)lv.size();
-        p->lv_offset = layout.size();
-        const float *f = reinterpret_cast<const float *>(lv.data() + 1);
-        layout.insert(layout.end(), f, f + (lv.size() - 1) * (sizeof(LevelDigits) / sizeof(float)));
-    } catch (const std::bad_alloc &) {
-        delete p;
-        return ISOQ_E_NOMEM;
+    // the levels as digits for the logits (of the widths with a tuned kernel);
+    // sets after the first go to the device with the rest
+    p->lv = LevelDigits{};
+    p->n_pass = 1;
+    p->wide = false;
+    p->lv_offset = 0;
+    if (decode_d(d)) {
+        std::vector<LevelDigits> lv;
+        try {
+            p->wide = !build_level_digits(bits, p->levels, lv);
+            while (layout.size() % 4)
+                layout.push_back(0.f);
+            p->lv = lv[0];
+            p->n_pass = (int)lv.size();
+            p->lv_offset = layout.size();
+            const float *f = reinterpret_cast<const float *>(lv.data() + 1);
+            layout.insert(layout.end(), f, f + (lv.size() - 1) * (sizeof(LevelDigits) / sizeof(float)));
+        } catch (const std::bad_alloc &) {
+            delete p;
+            return ISOQ_E_NOMEM;
+        }
     }
 
     hipError_t e = hipGetDevice(&p->device);

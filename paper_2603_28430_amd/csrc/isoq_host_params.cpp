@@ -475,25 +475,41 @@ bool build_level_digits(int bits, const float *levels, std::vector<LevelDigits> 
     }
     out.clear();
     long smallest = 0;   // integer of the first set
+    double enough = 0;   // squared errors of 2^-29 in the root mean square
+    for (int k = 0; k < H; k++)
+        enough += 0x1p-58 * level[k] * level[k];
     for (;;) {
         double big = 0;
         for (int k = 0; k < H; k++)
             big = std::max(big, std::fabs(rest[k]));
-        // the quantum (a float) whose integers come closest to every level in
-        // units of that level: the best of 2^17, or the first within 2^-26
-        // (16 Lloyd-Max levels: 0.9 x 2^-24 in the median over d; chosen by
-        // the sum of squared errors, the smallest was off by 4 to 14 x 2^-24)
-        double best = INFINITY, q = 1.0;
+        // The quantum (a float): of 2^13 between big / top and twice that,
+        // taken so that the smallest level is a whole number of them (it asks
+        // for the most), the one of the least sum of squared errors among those
+        // that leave no level further off than 2^-24 of itself, as a float
+        // would; or else the one of the least largest relative error.  (16
+        // Lloyd-Max levels, median over d: the worst level off by 0.9 x 2^-24
+        // of itself, the root mean square over keys 0.5 x 2^-24; chosen from
+        // 1,024 by the squares alone 4.7 and 0.8.)
+        double best = INFINITY, best_sum = INFINITY, q = 1.0;
         const double round = 6755399441055744.0;   // 1.5 x 2^52: adding and subtracting it rounds to an integer
-        for (int i = 0; i < 131072 && big > 0 && best > 0x1p-26; i++) {
-            const double qi = (double)(float)(big / top * (1.0 + i / 131072.0)), inv = 1.0 / qi;
-            double err = 0;   // in units of the quantum; the smallest level, first, settles most candidates
-            for (int k = 0; k < H && err * qi < best; k++) {
-                const double u = rest[k] * inv - half;
-                err = std::max(err, std::fabs(u - ((u + round) - round)) * per_level[k]);
+        const double lo = big / top, n_hi = std::fabs(rest[0]) / lo - half, n_lo = n_hi / 2 - half / 2;
+        const int tries = 8192;
+        const double step = std::max(1.0, std::floor((n_hi - n_lo) / tries));
+        for (int i = 0; i < tries && big > 0 && !(best == 0x1p-24 && best_sum <= enough); i++) {
+            const double n = std::floor(n_hi) - i * step;
+            const double qi = (double)(float)(n + half >= 256 ? std::fabs(rest[0]) / (n + half) : lo * (1.0 + (double)i / tries));
+            const double inv = 1.0 / qi;
+            double err = 0, sum = 0;   // in units of the quantum
+            for (int k = 0; k < H && err * qi < std::max(best, 0x1p-24); k++) {
+                const double u = rest[k] * inv - half, d = std::fabs(u - ((u + round) - round));
+                err = std::max(err, d * per_level[k]);
+                sum += d * d;
             }
-            if (qi > 0 && err * qi < best) {
-                best = err * qi;
+            err = std::max(err * qi, 0x1p-24);
+            sum *= qi * qi;
+            if (qi >= lo && qi < 2.01 * lo && (err < best || (err == best && sum < best_sum))) {
+                best = err;
+                best_sum = sum;
                 q = qi;
             }
         }
