@@ -478,11 +478,17 @@ bool build_level_digits(int bits, const float *levels, std::vector<LevelDigits> 
     double enough = 0;   // squared errors of 2^-29 in the root mean square
     for (int k = 0; k < H; k++)
         enough += 0x1p-58 * level[k] * level[k];
+    if (level[H - 1] == 0) {   // every level is zero as a float
+        out.push_back(LevelDigits{});
+        return true;
+    }
     for (;;) {
         double big = 0;
         for (int k = 0; k < H; k++)
             big = std::max(big, std::fabs(rest[k]));
-        // The quantum (a float): of 2^13 between big / top and twice that,
+        if (!out.empty() && big / top < 1e-37)   // (a level of zero) what is left is no ordinary float
+            return false;
+        // The quantum (a float): of 2^13 (4 bits) or 2^11 between big / top and twice that,
         // taken so that the smallest level is a whole number of them (it asks
         // for the most), the one of the least sum of squared errors among those
         // that leave no level further off than 2^-24 of itself, as a float
@@ -493,12 +499,12 @@ bool build_level_digits(int bits, const float *levels, std::vector<LevelDigits> 
         double best = INFINITY, best_sum = INFINITY, q = 1.0;
         const double round = 6755399441055744.0;   // 1.5 x 2^52: adding and subtracting it rounds to an integer
         const double lo = big / top, n_hi = std::fabs(rest[0]) / lo - half, n_lo = n_hi / 2 - half / 2;
-        const int tries = 8192;
+        const int tries = bits == 4 ? 8192 : 2048;
         const double step = std::max(1.0, std::floor((n_hi - n_lo) / tries));
-        for (int i = 0; i < tries && big > 0 && !(best == 0x1p-24 && best_sum <= enough); i++) {
+        for (int i = 0; i < tries && !(best == 0x1p-24 && best_sum <= enough); i++) {
             const double n = std::floor(n_hi) - i * step;
-            const double qi = (double)(float)(n + half >= 256 ? std::fabs(rest[0]) / (n + half) : lo * (1.0 + (double)i / tries));
-            const double inv = 1.0 / qi;
+            const double ideal = n + half >= 256 ? std::fabs(rest[0]) / (n + half) : lo * (1.0 + (double)i / tries);
+            const double qi = (double)(float)ideal, inv = 1.0 / qi;
             double err = 0, sum = 0;   // in units of the quantum
             for (int k = 0; k < H && err * qi < std::max(best, 0x1p-24); k++) {
                 const double u = rest[k] * inv - half, d = std::fabs(u - ((u + round) - round));

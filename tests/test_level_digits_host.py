@@ -32,6 +32,9 @@ def test_level_digits(tmp_path):
         for ratio in (2.0, 50.0, 1e3, 1e6):
             pos = 0.3 * ratio ** (np.arange(k) / (k - 1) - 1.0)
             books.append((b, np.concatenate([-pos[::-1], pos]), None))
+        zero = np.concatenate([[1e-60], 0.1 + np.arange(1, k) / 7.0])   # (a level that is zero as a float)
+        books.append((b, np.concatenate([-zero[::-1], zero]), None))
+        books.append((b, np.concatenate([-zero[::-1], zero]) * 1e-60, 1))
     # codebooks at the ends of the range of floats
     books += [(b, c * scale, sets) for b, c, sets in books[:30:5] for scale in (2.0 ** -115, 2.0 ** 120)]
     text = "".join("%d %s\n" % (b, " ".join("%.9g" % np.float32(v) for v in c)) for b, c, _ in books)
@@ -42,7 +45,7 @@ def test_level_digits(tmp_path):
         n, narrow, *vals = line.split()
         vals, ref = np.array(vals, float), np.float32(c).astype(float)
         assert 1 <= int(n) < 8 and (sets is None or int(n) == sets), (b, n)
-        assert np.all(np.abs(vals - ref) <= 2.0 ** -23 * np.abs(ref)), (b, vals / ref - 1)
+        assert np.all(np.abs(vals - ref) <= 2.0 ** -23 * np.abs(ref) + 1e-30), (b, vals / ref - 1)
         assert np.array_equal(vals, -vals[::-1])
         # the short sum: the Lloyd-Max codebooks, not those of distant levels
         assert int(narrow) if sets else not (int(narrow) and ref[-1] > 64 * ref[len(ref) // 2])
