@@ -165,9 +165,9 @@ constexpr int kScoreChunk = 1024;
 // tables (isoq_scores.h) rather than the matrix cores (isoq_scores_m.h).  One
 // head alone does not pay for spreading a key's indices over selector bytes
 // (measured 8-40% slower than the tables at every width up to 256), except
-// where the tables need more than 64 KB of LDS (d = 512, 3 and 4 bits: 97 and
-// 121 us with tables, 30 and 40 us on the matrix cores; 4 x 16 heads, 8,192
-// keys).
+// where a workgroup's tables weigh most, d = 512 with 3 and 4 bits: 97 and 121
+// us with tables (256 of 64 entries, over 64 KB, two workgroups per CU; 512
+// lookups per key), 33 and 42 us on the matrix cores (4 x 16 heads, 8,192 keys).
 constexpr bool score_by_tables(int d, int bits, int group) { return group == 1 && !(d == 512 && bits >= 3); }
 
 // Score kernel for (variant, d, bits, fp16 queries?, -inf where there is no

@@ -1,7 +1,7 @@
 // Attention logits against a paged cache of quantized keys, for decoding, on
 // the integer matrix cores: groups of two or more query heads per key head
 // (grouped-query attention), and single heads where the lookup tables of
-// isoq_scores.h do not fit (see score_by_tables).
+// isoq_scores.h are slower (see score_by_tables).
 //
 // A key stored by isoq_kv_append is x_hat = rho T^{-1}(c[idx]) with T the
 // block rotation of its head.  T is orthogonal (Prop. 1), so for a query q
@@ -20,8 +20,10 @@
 // that the integers hit the levels (build_level_digits); a codebook that one
 // set of digits does not hold to 2^-23 of each level, or whose smallest level is
 // far below the largest, is `wide` (MP): every digit product, and passes over
-// the residual levels.  Against 64 bits the logits are off by 5e-8 of their
-// rms; the fp32 lookup tables that this replaces were off by 1.3e-7.
+// the residual levels.  Against 64 bits the logits are off by 7e-8 to 8e-8 of
+// their rms (d = 128 and 512, 2 to 4 bits, with and without the sketch); the
+// fp32 lookup tables that this replaces were off by 1.2e-7 to 1.7e-7 at d = 128
+// and 2.2e-7 to 3.0e-7 at d = 512.
 //
 // Why digits.  A level digit is a byte picked by a 3-bit index, which is what
 // v_perm_b32 does for four coordinates at once: a quad of coordinates costs
@@ -30,12 +32,13 @@
 // work.  Lookup tables of the query (one LDS read, shift, and-or and add per
 // two coordinates and query head) are bound by LDS reads and VALU issue in
 // proportion to the heads of a group.  What bounds this kernel is VALU issue
-// too (about 400 instructions per 64 keys at d = 128, 3 bits, 4 heads; the
-// matrix cores are busy an eighth of the time), but once per key.  Measured at
-// 8 sequences x 32,768 keys x 8 key heads, d = 128, tables -> digits: 4 heads,
-// 2 / 3 / 4 bits 49 / 88 / 86 -> 30 / 35 / 44 us, with 128 sketch bits
-// 111 / 156 / 162 -> 50 / 50 / 60 us; 8 heads (4 key heads), 3 bits 124 -> 26 us;
-// 2 heads (16 key heads, 16,384 keys), 3 bits 43 -> 31 us.
+// too (counters, preparation included: 422 instructions per 64 keys at d = 128,
+// 3 bits, 4 heads, 24 of them matrix instructions; the matrix cores are busy an
+// eighth of the time), but once per key.  Measured at 8 sequences x 32,768 keys
+// x 8 key heads, d = 128, tables -> digits: 4 heads, 2 / 3 / 4 bits 45 / 88 / 83
+// -> 28 / 34 / 43 us, with 128 sketch bits 109 / 156 / 161 -> 44 / 50 / 57 us; 8
+// heads (4 key heads), 3 bits 125 -> 26 us; 2 heads (16 key heads, 16,384 keys),
+// 3 bits 43 -> 31 us.
 //
 // Lane layout.  A lane loads one key of the wave's 64 (its record's pieces,
 // norm and sketch: consecutive lanes read consecutive bytes of the piece-major

@@ -665,16 +665,20 @@ struct Stage1M {
     // project together: wave w loads the 16 rows of S' of column tile w mod NT
     // into registers and takes every row block of 16 (m = 64: every second
     // one), so S' needs no LDS and the block's only LDS is E and the signs
-    // (34 KB at d = m = 128).  The kernel is bound by VALU issue (about 165
-    // instructions per 4 rows at 3 bits) and the matrix instructions that
-    // share it.  With S' staged in LDS, blocks walked several tiles (to stage
-    // it less often), which took 110 registers and held a CU to two blocks of
-    // eight waves; a block of one tile takes 54.  Measured at d = 128, m =
-    // 128, 3 bits: 1,000,003 rows 108.4 -> 106.6 us, append of 8 x 4,096
-    // tokens x 32 heads 125.9 -> 117.9 us; d = 64 quantize 5% less, d = 256
-    // quantize 5% and append 8% less.  The products are those of qjl_project
-    // (k steps in order, fp32 accumulation), with the errors negated: the sign
-    // bit of a result is the sketch bit.
+    // (34 KB at d = m = 128).  VALU issue bounds the kernel: 198 instructions
+    // per 4 rows at d = m = 128, 3 bits (224 for the append; counters, 12 of
+    // them matrix instructions) are 84 (95) us of 1M rows' 106 (117) at four
+    // cycles each.  With S' staged in LDS, blocks walked several tiles (to
+    // stage it less often) in 183 (215) instructions, but with 110 registers,
+    // which held a CU to two blocks of eight waves; a block of one tile takes
+    // 53 (65).  Measured at d = 128, m = 128, 3 bits, several tiles -> one:
+    // 1,000,003 rows 108.7 -> 105.8 us (109.1 both on another box), append of 8
+    // x 4,096 tokens x 32 heads 125.8 -> 116.4 us; d = 64, m = 64: 53.7 -> 48.0
+    // us; d = 256, m = 64, 400,003 rows 82.1 -> 77.5 us.  Single decode tokens
+    // at 2 and 3 bits are up to 7% (0.3 us) slower than with staged S'.  The
+    // products are those of qjl_project (k steps in order, fp32 accumulation),
+    // with the errors negated: the sign bit of a result is the sketch bit (a
+    // sum within its last rounding of zero may differ: 1 bit in 10^8).
     static constexpr int NT = QM / 16 > 0 ? QM / 16 : 1;              // column tiles of S'
     static constexpr int kTilesPerWave = NT > WAVES ? NT / WAVES : 1;  // a wave's: w mod NT, + WAVES, ...
     static constexpr int kWavesPerTile = WAVES > NT ? WAVES / NT : 1;  // which share its row blocks
